@@ -891,7 +891,8 @@ struct StageTimer {
 // Runs the whole evaluation pipeline for `count` plans whose views are in V.
 // Plans with different orders get separate launches of the order-templated
 // kernels; everything else is one launch per stage for all plans.
-int run_pipeline(fmm_plan_s *const *P, int count, const PlanView *V, hipStream_t s)
+// fld: nonzero if any plan of the call is given a field array.
+int run_pipeline(fmm_plan_s *const *P, int count, const PlanView *V, int fld, hipStream_t s)
 {
     // (no heap allocation here: the batched entry point without allocation
     // runs this too)
@@ -927,7 +928,7 @@ int run_pipeline(fmm_plan_s *const *P, int count, const PlanView *V, hipStream_t
                 Bq.n = j - i;
                 Bq.b[0] = 0;
                 for (int t = 0; t < j - i; ++t) Bq.b[t + 1] = Bq.b[t] + stage_blocks(P[i + t]).p2p[part];
-                launch_p2p(mixed, part, V + i, Bq, F->side);
+                launch_p2p(mixed, fld, part, V + i, Bq, F->side);
                 i = j;
             }
         }
@@ -1014,7 +1015,7 @@ int run_pipeline(fmm_plan_s *const *P, int count, const PlanView *V, hipStream_t
             int w = 0;
             for (int i = r.first; i < r.second; ++i) w += P[i]->nlist[2] > 0;
             if (w)
-                launch_m2p(P[r.first]->p, V + r.first,
+                launch_m2p(P[r.first]->p, fld, V + r.first,
                            sub(r.first, r.second, [](const fmm_plan_s *p) { return p->nlist[2] > 0 ? p->nleaves : 0; }), F->side);
         }
         T2.end();
@@ -1048,7 +1049,7 @@ int run_pipeline(fmm_plan_s *const *P, int count, const PlanView *V, hipStream_t
     HIPCHK(hipStreamWaitEvent(s, F->ev_join, 0));
     T.begin(8);
     for (auto &r : runs)
-        launch_far(P[r.first]->p, V + r.first,
+        launch_far(P[r.first]->p, fld, V + r.first,
                    sub(r.first, r.second, [](const fmm_plan_s *p) { return stage_blocks(p).far; }), s);
     T.end();
     HIPCHK(hipGetLastError());
@@ -1061,7 +1062,7 @@ int run_pipeline(fmm_plan_s *const *P, int count, const PlanView *V, hipStream_t
 // second part and M2P (W lists) beside P2L (X lists) and the L2L.  P2M raw
 // moments -> moments, M2M by one-axis shifts, M2L on the full components with
 // the level's tables, L2L by one-axis shifts, then L2P with the near field.
-int run_soft(fmm_plan_s *P, hipStream_t s)
+int run_soft(fmm_plan_s *P, int fld, hipStream_t s)
 {
     const PlanView *V = P->view_dev;
     StageTimer T(P, s);
@@ -1082,11 +1083,11 @@ int run_soft(fmm_plan_s *P, hipStream_t s)
         HIPCHK(hipEventRecord(P->ev_fork, s));
         HIPCHK(hipStreamWaitEvent(P->side, P->ev_fork, 0));
         T2.begin(9 + part);
-        launch_p2p(2, part, V, one(sp.p2p[part]), P->side);
+        launch_p2p(2, fld, part, V, one(sp.p2p[part]), P->side);
         T2.end();
         if (part == 1 && P->nlist[2] > 0) { // M2P adds into the near-field sums
             T2.begin(11);
-            launch_soft_m2p(P->p, V, P->nleaves, P->side);
+            launch_soft_m2p(P->p, fld, V, P->nleaves, P->side);
             T2.end();
         }
         HIPCHK(hipEventRecord(P->ev_join, P->side));
@@ -1134,7 +1135,7 @@ int run_soft(fmm_plan_s *P, hipStream_t s)
     T.end();
     HIPCHK(hipStreamWaitEvent(s, P->ev_join, 0));
     T.begin(8);
-    launch_far(P->p, V, one(sp.far), s);
+    launch_far(P->p, fld, V, one(sp.far), s);
     T.end();
     HIPCHK(hipGetLastError());
     return 0;
@@ -1155,7 +1156,8 @@ extern "C" int fmm_evaluate(fmm_plan_t plan, const double *q_dev, double *phi_de
     v.fld_out = field_dev;
     HIPCHK(hipMemcpyAsync(P->view_dev, &v, sizeof(PlanView), hipMemcpyHostToDevice, stream));
     fmm_plan_s *arr[1] = {P};
-    int rc = P->kernel == FMM_KERNEL_SOFTENED ? run_soft(P, stream) : run_pipeline(arr, 1, P->view_dev, stream);
+    const int fld = field_dev != nullptr;
+    int rc = P->kernel == FMM_KERNEL_SOFTENED ? run_soft(P, fld, stream) : run_pipeline(arr, 1, P->view_dev, fld, stream);
     if (rc) return rc;
     if (P->note_use(stream)) return fail(FMM_EDEVICE, "event record failed");
     return FMM_OK;
@@ -1199,6 +1201,7 @@ int batch_chunk(fmm_plan_t const *plans, const int *idx, int c0, int c1, const d
     fmm_plan_s *P[kMaxBatch];
     PlanView views[kMaxBatch];
     const int m = c1 - c0;
+    int fld = 0;
     for (int t = 0; t < m; ++t) {
         const int i = idx[c0 + t];
         P[t] = plans[i];
@@ -1206,9 +1209,10 @@ int batch_chunk(fmm_plan_t const *plans, const int *idx, int c0, int c1, const d
         views[t].q_in = q_dev[i];
         views[t].phi_out = phi_dev[i];
         views[t].fld_out = field_dev ? field_dev[i] : nullptr;
+        fld |= views[t].fld_out != nullptr;
     }
     HIPCHK(hipMemcpyAsync(Vd, views, sizeof(PlanView) * m, hipMemcpyHostToDevice, stream));
-    return run_pipeline(P, m, Vd, stream);
+    return run_pipeline(P, m, Vd, fld, stream);
 }
 
 int batch_note_use(fmm_plan_t const *plans, int32_t count, hipStream_t stream)

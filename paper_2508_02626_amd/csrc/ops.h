@@ -25,13 +25,14 @@ void launch_parent_mh(const PlanView *V, const Bases &B, int full, hipStream_t s
 void launch_unfold(int p, const PlanView *V, const Bases &B, int leaves_only, hipStream_t s); // kRemapBoxes boxes/block
 void launch_p2l(int p, const PlanView *V, const Bases &B, hipStream_t s);  // 1 X target/block
 void launch_p2l_transform(const PlanView *V, const Bases &B, hipStream_t s); // 16 X targets x 16 rows/block
-void launch_far(int p, const PlanView *V, const Bases &B, hipStream_t s);  // 2 leaves/block (L2P + output)
-void launch_m2p(int p, const PlanView *V, const Bases &B, hipStream_t s);  // 1 leaf/block (W lists)
+void launch_far(int p, int fld, const PlanView *V, const Bases &B, hipStream_t s);  // 2 leaves/block (L2P + output)
+void launch_m2p(int p, int fld, const PlanView *V, const Bases &B, hipStream_t s);  // 1 leaf/block (W lists)
 // P2P runs in two parts (leaves [0, split) and [split, nleaves)), each
 // overlapping a latency-bound phase of the far field
 __host__ __device__ inline int p2p_split(int nleaves) { return (int)((int64_t)nleaves * 5 / 8) & ~3; }
-// mixed: 0 FP64, 1 FP32 terms, 2 softened kernel (FP64)
-void launch_p2p(int mixed, int part, const PlanView *V, const Bases &B, hipStream_t s); // 4 leaves/block
+// mixed: 0 FP64, 1 FP32 terms, 2 softened kernel (FP64); fld (here, in
+// launch_far and launch_m2p): 0 when no plan of the launch asks for the field
+void launch_p2p(int mixed, int fld, int part, const PlanView *V, const Bases &B, hipStream_t s); // 4 leaves/block
 void launch_zero(double *p, int64_t n, hipStream_t s);
 void launch_zero_f32(float *p, int64_t n, hipStream_t s);
 void launch_m2l(int p, int f32, const PlanView *V, const Bases &B, hipStream_t s); // 64 slots/block

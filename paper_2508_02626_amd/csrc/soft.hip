@@ -1022,7 +1022,7 @@ __global__ __launch_bounds__(64) void k_soft_p2l(const PlanView *V)
 // W box are read from LDS (the same address on every lane), the next box's
 // prefetched into registers meanwhile.
 namespace m2p_detail {
-template <int P> struct Acc {
+template <int P, bool FLD> struct Acc {
     const double *m; // Mhat of the W box, m[NC] = 0
     double ph, g0, g1, g2;
     template <int E> __device__ __forceinline__ void on(double v)
@@ -1032,14 +1032,14 @@ template <int P> struct Acc {
         constexpr double gf = cx_gfact(E); // (a constant: no factorial at run time)
         const double b = v * gf;
         if constexpr (n <= P) ph = fma(m[E], b, ph);
-        if constexpr (i >= 1) g0 = fma(m[cx_index(i - 1, j, k)], b, g0);
-        if constexpr (j >= 1) g1 = fma(m[cx_index(i, j - 1, k)], b, g1);
-        if constexpr (k >= 1) g2 = fma(m[cx_index(i, j, k - 1)], b, g2);
+        if constexpr (FLD && i >= 1) g0 = fma(m[cx_index(i - 1, j, k)], b, g0);
+        if constexpr (FLD && j >= 1) g1 = fma(m[cx_index(i, j - 1, k)], b, g1);
+        if constexpr (FLD && k >= 1) g2 = fma(m[cx_index(i, j, k - 1)], b, g2);
     }
 };
 } // namespace m2p_detail
 
-template <int P>
+template <int P, bool FLD>
 __global__ __launch_bounds__(64) void k_soft_m2p(const PlanView *V)
 {
     constexpr int NC = ncoef(P), RC = (NC + 63) / 64;
@@ -1081,16 +1081,18 @@ __global__ __launch_bounds__(64) void k_soft_m2p(const PlanView *V)
             if (e + 1 < w1) src = fetch(e + 1);
             const double ih = 1.0 / hs, eta2 = v.eps2 * ih * ih;
             const double u[3] = {(px - cs[0]) * ih, (py - cs[1]) * ih, (pz - cs[2]) * ih};
-            m2p_detail::Acc<P> acc{cm[buf], 0.0, 0.0, 0.0, 0.0};
-            lane_taylor::taylor<P + 1>(u, eta2, acc);
+            m2p_detail::Acc<P, FLD> acc{cm[buf], 0.0, 0.0, 0.0, 0.0};
+            lane_taylor::taylor<FLD ? P + 1 : P>(u, eta2, acc); // (degree P + 1 is the gradient's)
             phi = fma(acc.ph, ih, phi);
-            const double ih2 = ih * ih;
-            gx = fma(acc.g0, ih2, gx);
-            gy = fma(acc.g1, ih2, gy);
-            gz = fma(acc.g2, ih2, gz);
+            if constexpr (FLD) {
+                const double ih2 = ih * ih;
+                gx = fma(acc.g0, ih2, gx);
+                gy = fma(acc.g1, ih2, gy);
+                gz = fma(acc.g2, ih2, gz);
+            }
         }
-        if (act) { // E = -grad phi
-            v.phi_near[i] += phi;
+        if (act) v.phi_near[i] += phi;
+        if (FLD && act) { // E = -grad phi
             v.fld_near[3 * (int64_t)i] -= gx;
             v.fld_near[3 * (int64_t)i + 1] -= gy;
             v.fld_near[3 * (int64_t)i + 2] -= gz;
@@ -1152,10 +1154,12 @@ void launch_soft_p2l(int p, const PlanView *V, int nxtgt, hipStream_t s)
 #undef T_
 }
 
-void launch_soft_m2p(int p, const PlanView *V, int nleaves, hipStream_t s)
+void launch_soft_m2p(int p, int fld, const PlanView *V, int nleaves, hipStream_t s)
 {
     if (nleaves <= 0) return;
-#define T_(PP) k_soft_m2p<PP><<<nleaves, 64, 0, s>>>(V)
+#define T_(PP)                                              \
+    if (fld) k_soft_m2p<PP, true><<<nleaves, 64, 0, s>>>(V); \
+    else k_soft_m2p<PP, false><<<nleaves, 64, 0, s>>>(V)
     SOFT_SWITCH(p, T_)
 #undef T_
 }
