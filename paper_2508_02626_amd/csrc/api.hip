@@ -428,7 +428,6 @@ int build_plan(fmm_plan_s *P, const double *xyz)
     }
     const int nb = P->nboxes;
     const bool soft = P->kernel == FMM_KERNEL_SOFTENED;
-    P->m2l_parts = (P->m2l_rot || soft) ? 1 : sym_m2l_parts(P->p);
     // the sign-class M2L addresses the folded multipoles with 32-bit byte offsets
     if (!soft && m2l_sym(P->p) && (unsigned long long)(nb + 1) * (unsigned long long)P->ldmh * 8ULL >= (1ULL << 32))
         return fail(FMM_EUNSUPPORTED, "too many boxes for this order (folded multipoles reach 4 GiB)");
@@ -450,7 +449,6 @@ int build_plan(fmm_plan_s *P, const double *xyz)
             if (ldms) o.add<double>((size_t)(nb + 1) * ldms);
         } else {
             o.add<double>((size_t)(nb + 1) * P->ldmh).add<double>((size_t)nb * P->ldh);
-            if (P->m2l_parts > 1 && !sym_parts_add(P->p)) o.add<double>((size_t)(P->m2l_parts - 1) * nb * P->ldh);
             if (P->mixed_m2l && m2l_f32_operands(P->p)) o.add<float>((size_t)(nb + 1) * P->ldmh);
         }
         if (!P->reserve(true, o.total)) return fail(FMM_ENOMEM, "device allocation failed (boxes)");
@@ -483,10 +481,6 @@ int build_plan(fmm_plan_s *P, const double *xyz)
     double *Mh = soft ? nullptr : P->own<double>((size_t)(nb + 1) * P->ldmh);
     double *Lh = soft ? nullptr : P->own<double>((size_t)nb * P->ldh);
     float *Mhf = P->mixed_m2l && m2l_f32_operands(P->p) ? P->own<float>((size_t)(nb + 1) * P->ldmh) : nullptr;
-    // orders >= 12: partial sums of the M2L class parts after the first
-    const bool lh2 = P->m2l_parts > 1 && !sym_parts_add(P->p);
-    double *Lh2 = lh2 ? P->own<double>((size_t)(P->m2l_parts - 1) * nb * P->ldh) : nullptr;
-    if (lh2) NOMEM(Lh2);
     double *Dsoft = nullptr, *zrow = nullptr;
     int *soft_map = nullptr;
     if (soft) {
@@ -567,8 +561,12 @@ int build_plan(fmm_plan_s *P, const double *xyz)
     int64_t slot_cap = ((int64_t)nt + 8 * (kM2LSlots - 1) + kM2LSlots - 1) / kM2LSlots * kM2LSlots;
     if (slot_cap < kM2LSlots) slot_cap = kM2LSlots;
     const int64_t mw = P->nlist[2];
+    P->m2l_parts = (P->m2l_rot || soft) ? 1 : m2l_parts_of(P->p, slot_cap / kM2LSlots, nb);
+    // partial sums of the M2L parts after the first
+    const bool lh2 = P->m2l_parts > 1 && !m2l_parts_add(P->p, P->m2l_parts);
     {
         Sizer o;
+        if (lh2) o.add<double>((size_t)(P->m2l_parts - 1) * nb * P->ldh);
         for (int w = 0; w < 4; ++w)
             if (w != 1) o.add<int32_t>(P->nlist[w] ? P->nlist[w] : 1);
         o.add<int32_t>(slot_cap);
@@ -586,6 +584,8 @@ int build_plan(fmm_plan_s *P, const double *xyz)
     }
     int32_t *slots = P->own<int32_t>(slot_cap);
     NOMEM(slots);
+    double *Lh2 = lh2 ? P->own<double>((size_t)(P->m2l_parts - 1) * nb * P->ldh) : nullptr;
+    if (lh2) NOMEM(Lh2);
     if (P->uniform) ulist_uniform(ta, 1, nullptr, nullptr, nullptr, P->off[0], P->src[0], s);
     else uwlist(ta, coll, 1, nullptr, P->off[0], P->src[0], nullptr, P->off[2], P->src[2], nullptr, s);
     if (mw > 0) { // X = transpose of W
@@ -936,10 +936,10 @@ int run_pipeline(fmm_plan_s *const *P, int count, const PlanView *V, int fld, hi
     };
     HIPCHK(hipEventRecord(F->ev_fork, s));
     HIPCHK(hipStreamWaitEvent(F->side, F->ev_fork, 0));
-    // Lh rows zeroed for the M2L class parts to add into (orders 6-11; the
-    // M2L waits for the side stream's first part)
+    // Lh rows zeroed where the M2L parts add into them (the M2L waits for the
+    // side stream's first part)
     launch_lh_zero(V, sub(0, count, [](const fmm_plan_s *p) {
-        return p->m2l_parts > 1 && sym_parts_add(p->p) ? (int)ceil_div((int64_t)p->nboxes * p->ldh, 512) : 0; }), F->side);
+        return m2l_parts_add(p->p, p->m2l_parts) ? (int)ceil_div((int64_t)p->nboxes * p->ldh, 512) : 0; }), F->side);
     p2p_part(0);
     HIPCHK(hipEventRecord(F->ev_join, F->side));
     // runs of equal order (callers sort batches by order)
@@ -1029,9 +1029,9 @@ int run_pipeline(fmm_plan_s *const *P, int count, const PlanView *V, int fld, hi
         launch_p2l_transform(V + r.first, sub(r.first, r.second, [](const fmm_plan_s *p) {
             return (int)ceil_div(p->nxtgt, 16) * (p->ldh / 16); }), s);
     // complete Lh rows of plans whose M2L stores them (zero where nothing
-    // arrived, plus the second part of the sign classes from order 12)
+    // arrived, plus the sums of the M2L parts after the first)
     launch_lh_init(V, sub(0, count, [](const fmm_plan_s *p) {
-        return p->m2l_parts > 1 && sym_parts_add(p->p) ? 0 : (int)ceil_div(p->nboxes, 4); }), s);
+        return m2l_parts_add(p->p, p->m2l_parts) ? 0 : (int)ceil_div(p->nboxes, 4); }), s);
     T.end();
     // L2L on the harmonic components, then full local expansions at the leaves
     T.begin(7);
@@ -1276,10 +1276,12 @@ extern "C" int fmm_plan_estimate(int64_t n, int32_t order, int32_t leaf_size, co
         boxes = 1 + 8.0 * 2.0 * n / (leaf_size + 1);
     }
     double ldm = pad16(ncoef(order)), ldh = pad16(nharm(order)), ldmh = folded_ld(order);
-    const int parts = sym_parts_add(order) ? 1 : sym_m2l_parts(order);
+    const int parts = m2l_parts_add(order, m2l_base_parts(order)) ? 1 : m2l_base_parts(order);
     double per_box = 8 * (2 * ldm + parts * ldh + ldmh) + 4 * ldmh + 4 * 200 + 64; // expansions, slots, lists
+    // slices of the M2L parts of small trees
+    const double slices = 8 * ldh * std::min((kM2LMaxParts - 1) * boxes, (double)kM2LSliceRows);
     double per_particle = 8 * 3 + 4 + 8 * 5 + 8 * 2;
-    double total = boxes * per_box + n * per_particle + 8 * 27 * boxes;
+    double total = boxes * per_box + slices + n * per_particle + 8 * 27 * boxes;
     const int depth = o.uniform_depth >= 0 ? o.uniform_depth : o.max_depth;
     if (o.kernel == FMM_KERNEL_SOFTENED && depth >= 2 && order <= kSoftMaxOrder)
         total += 8.0 * (depth - 1) * 343 * soft_table_ldc(order); // derivative tables per level (at most)

@@ -122,22 +122,39 @@ __host__ __device__ constexpr int sym_ksteps(int p)
 }
 // orders whose M2L runs on sign classes (fewer matrix-core products from p = 6 on)
 __host__ __device__ constexpr bool m2l_sym(int p) { return p >= 6; }
-// blocks per M2L tile of 64 targets at sign-class orders: the tile's classes
-// are split into this many contiguous parts by matrix-core work, each block
-// writing its own partial sums.  Two: more, shorter blocks did not shorten the
-// launch's tail as much as their per-block set-up cost (uniform 10^6 points,
-// p = 8, equal parts: 0.97 ms with two, 0.96 with three, 1.07 with four; on a
-// Plummer tree three were slower than two).
-__host__ __device__ constexpr int sym_m2l_parts(int p) { return m2l_sym(p) ? 2 : 1; }
-// Orders 6-11: the parts add their sums into Lh rows zeroed before the M2L,
-// with FP64 atomics (two addends onto zero give the same sum in either order,
-// more would not), so no pass over partial sums follows the launch (uniform
-// 10^6 points, p = 8: 2.36 against 2.56 ms per step).  From order 12 the
-// second part stores its sums to a slice of its own and the pass before the
-// L2L adds them (the atomics slowed the p = 14 launch by 3%, more than that
-// pass takes).
-__host__ __device__ constexpr bool sym_parts_add(int p) { return m2l_sym(p) && p <= 11; }
-static_assert(sym_m2l_parts(6) <= 2 && sym_m2l_parts(11) <= 2, "M2L parts add into Lh in any order");
+// blocks per M2L tile of 64 targets (m2l_parts of a plan with `tiles` of them).
+// Trees that fill the chip with base_parts blocks per tile: at sign-class
+// orders the tile's classes are split into two contiguous parts by matrix-core
+// work; more, shorter blocks did not shorten the launch's tail as much as
+// their per-block set-up cost (uniform 10^6 points, p = 8, equal parts: 0.97 ms
+// with two, 0.96 with three, 1.07 with four; on a Plummer tree three were
+// slower than two).  Smaller trees leave CUs idle while each block walks its
+// classes (or, below order 6, slots) one after the other, about 4 us each: they
+// split a tile into as many parts as bring the launch to about kM2LFillBlocks
+// blocks, one per CU.  2000 points, p = 6, depth 3 (16 tiles): M2L 205 us with
+// two parts, 53 with 16 (a
+// target of 512 blocks: the same at 1e3 to 1e5 points, slower batches).
+// (The slices of partial sums are bounded to kM2LSliceRows rows, whatever
+// the share of boxes with a V list.)
+constexpr int kM2LFillBlocks = 256, kM2LMaxParts = 16, kM2LSliceRows = 2 * 64 * kM2LFillBlocks;
+__host__ __device__ constexpr int m2l_base_parts(int p) { return m2l_sym(p) ? 2 : 1; }
+__host__ __device__ constexpr int m2l_parts_of(int p, int64_t tiles, int64_t nboxes)
+{
+    const int base = m2l_base_parts(p);
+    if (tiles < 1 || nboxes < 1 || tiles * base >= kM2LFillBlocks) return base;
+    int64_t n = (kM2LFillBlocks + tiles - 1) / tiles;
+    if (n > kM2LMaxParts) n = kM2LMaxParts;
+    if (n > 1 + kM2LSliceRows / nboxes) n = 1 + kM2LSliceRows / nboxes;
+    return (int)(n > base ? n : base);
+}
+// Orders 6-11 with two parts: the parts add their sums into Lh rows zeroed
+// before the M2L, with FP64 atomics (two addends onto zero give the same sum in
+// either order, more would not), so no pass over partial sums follows the
+// launch (uniform 10^6 points, p = 8: 2.36 against 2.56 ms per step).  With
+// more parts, and from order 12 (the atomics slowed the p = 14 launch by 3%,
+// more than that pass takes), every part after the first stores its sums to a
+// slice of its own and the pass before the L2L adds them in part order.
+__host__ __device__ constexpr bool m2l_parts_add(int p, int parts) { return m2l_sym(p) && p <= 11 && parts == 2; }
 // share (percent) of a tile's matrix-core work in its first part; the launch
 // runs the first parts before the others (longest first), so that its end is
 // made of the shorter blocks (uniform 10^6 points, p = 8, FP64: about 6%
@@ -345,9 +362,9 @@ struct PlanView {
     // evaluation buffers
     double *qs;                         // sorted charges
     double *M, *Mh, *Lh, *L;            // [boxes][ldm] / [boxes][ldmh] / [boxes][ldh]
-    double *Lh2;                        // orders >= 12: [m2l_parts - 1][boxes][ldh] partial sums
-                                        // of the M2L class parts after the first (else null)
-    int m2l_parts;                      // blocks per M2L tile (1 below the sign-class orders)
+    double *Lh2;                        // [m2l_parts - 1][boxes][ldh] partial sums of the M2L parts
+                                        // after the first (null where the parts add into Lh)
+    int m2l_parts;                      // blocks per M2L tile
     float *Mhf;                         // FP32 folded multipoles (mixed M2L)
     // softened kernel 1/sqrt(|x|^2 + eps^2) (kernel == 1): full Cartesian
     // expansions in M and L, derivative tables per level

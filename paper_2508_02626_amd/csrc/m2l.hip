@@ -112,11 +112,14 @@ __global__ __launch_bounds__(256) void k_m2l(const PlanView *V, Bases B)
     __shared__ int sList[kVSlots];
     __shared__ int sSrc[64][kVSlots]; // slot rows of the block's targets
     __shared__ int sDoff[kVSlots];     // derivative table of each slot of this octant
-    __shared__ int sN, soct;
+    __shared__ unsigned long long sAny[4]; // slots used, 64 per wavefront
+    __shared__ int soct;
 
     const int k = find_plan(B, blockIdx.x);
     const PlanView &v = V[k];
-    const int tile = xcd_remap(blockIdx.x - B.b[k], B.b[k + 1] - B.b[k]);
+    // m2l_parts blocks per tile, each taking an equal share of its used slots
+    const int parts = v.m2l_parts;
+    const int item = xcd_remap(blockIdx.x - B.b[k], B.b[k + 1] - B.b[k]), tile = item / parts, part = item - tile * parts;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, col = lane & 15, kq = lane >> 4;
     const int tw = RS > 1 ? wave & 3 : wave, half = RS > 1 ? wave >> 2 : 0; // target group, row share
     // lanes col, col+16, col+32, col+48 serve target tw*16+col (one B column)
@@ -142,27 +145,38 @@ __global__ __launch_bounds__(256) void k_m2l(const PlanView *V, Bases B)
     // the block, in increasing order
     {
         const auto vs = gptr(v.vslot);
-        for (int e = tid; e < 64 * kVSlots; e += NT) {
-            const int t = e / kVSlots, j = e - t * kVSlots, g = sTg[t];
-            sSrc[t][j] = g >= 0 ? vs[(int64_t)g * kVSlots + j] : -1;
+        constexpr int NE = 64 * kVSlots, PER = (NE + NT - 1) / NT;
+        int val[PER]; // every load issued before the first is used
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int e = tid + NT * i < NE ? tid + NT * i : NE - 1, t = e / kVSlots, j = e - t * kVSlots;
+            val[i] = vs[(int64_t)max(sTg[t], 0) * kVSlots + j];
+        }
+        if (tid < kVSlots) sDoff[tid] = gptr(tb.offs)[soct * kVSlots + tid] * LDC;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int e = tid + NT * i, t = e / kVSlots, j = e - t * kVSlots;
+            if (e < NE) sSrc[t][j] = sTg[t] >= 0 ? val[i] : -1;
         }
     }
     __syncthreads();
+    int any = 0;
     if (tid < kVSlots) {
-        int any = 0;
+#pragma unroll 16
         for (int t = 0; t < 64; ++t) any |= sSrc[t][tid] >= 0;
-        sList[tid] = any;
-        sDoff[tid] = gptr(tb.offs)[soct * kVSlots + tid] * LDC;
     }
+    const unsigned long long mine = __ballot(any);
+    if (lane == 0) sAny[wave] = mine;
     __syncthreads();
-    if (tid == 0) {
-        int n = 0;
-        for (int j = 0; j < kVSlots; ++j)
-            if (sList[j]) sList[n++] = j;
-        sN = n;
+    int nbelow = __popcll(mine & lanes_below(lane)), nused = 0;
+    for (int w = 0; w < 4; ++w) {
+        const int c = __popcll(sAny[w]);
+        nbelow += w < wave ? c : 0;
+        nused += c;
     }
+    if (any) sList[nbelow] = tid;
     __syncthreads();
-    const int nvalid = sN, ldh = v.ldmh;
+    const int qa = nused * part / parts, nvalid = nused * (part + 1) / parts, ldh = v.ldmh;
     const T *Dt = Mfma<T>::D(tb);
     const T *Mh = Mfma<T>::M(v);
     const int *vsl = sSrc[tw * 16 + col];
@@ -221,10 +235,10 @@ __global__ __launch_bounds__(256) void k_m2l(const PlanView *V, Bases B)
         else pb[buf] = val;
     };
     int src = -1;
-    if (nvalid > 0) {
-        load_d(sList[0]);
+    if (nvalid > qa) {
+        load_d(sList[qa]);
         store_d(0);
-        src = vsl[sList[0]];
+        src = vsl[sList[qa]];
 #pragma unroll
         for (int t = 0; t < NW; ++t) load_b(t, t, src);
         if constexpr (DB) {
@@ -233,8 +247,8 @@ __global__ __launch_bounds__(256) void k_m2l(const PlanView *V, Bases B)
         }
         __syncthreads();
     }
-    for (int q = 0; q < nvalid; ++q) {
-        const int cur = q & 1;
+    for (int q = qa; q < nvalid; ++q) {
+        const int cur = (q - qa) & 1;
         const bool more = q + 1 < nvalid;
         const int jn = more ? sList[q + 1] : 0;
         if (more) load_d(jn); // in flight during the products
@@ -308,7 +322,7 @@ __global__ __launch_bounds__(256) void k_m2l(const PlanView *V, Bases B)
         xs[x] = t;
     }
     if (tgt < 0) return;
-    double *Lh = v.Lh + (int64_t)tgt * ldh;
+    double *Lh = (part ? v.Lh2 + (int64_t)(part - 1) * v.nboxes * v.ldh : v.Lh) + (int64_t)tgt * ldh;
 #pragma unroll
     for (int mt = 0; mt < MTW; ++mt)
 #pragma unroll
@@ -344,13 +358,13 @@ __global__ __launch_bounds__(256) void k_m2l(const PlanView *V, Bases B)
 // count them) two vectors ahead, across class boundaries (all eight members
 // for the next class, whose mask is not known there).  m2l_parts blocks share
 // a tile, each running a contiguous part of its classes (the first with
-// kSymFirstPart % of the matrix-core work, dispatched before the others),
-// and adds its sums into the target rows of Lh, zeroed before the launch, with
-// FP64 atomics: with two parts each entry receives 0 + a + b in either order,
+// kSymFirstPart % of the matrix-core work, dispatched before the others).
+// Two parts add their sums into the target rows of Lh, zeroed before the
+// launch, with FP64 atomics: each entry receives 0 + a + b in either order,
 // which is exact-order independent (a + b = b + a), so the result does not
-// depend on which part finishes first.  (k_m2l_symh, orders >= 12: part i > 0
-// writes its partial sums to slice i - 1 of Lh2, which the pass before the L2L
-// adds in part order.)
+// depend on which part finishes first.  With more parts (small trees) and in
+// k_m2l_symh (orders >= 12) part i > 0 writes its partial sums to slice i - 1 of
+// Lh2, which the pass before the L2L adds in part order.
 template <int P> struct SymShape {
     static constexpr int RT = sym_row_tiles(P), KS = sym_ksteps(P);
     int rc[RT], kc[KS]; // parity class of each row tile and k-step
@@ -385,10 +399,9 @@ template <typename T> __device__ inline void wht8(T (&h)[8])
 // classes end in the list (sZend; the table orders classes by zero mask) and
 // pick the range [sQa, sQb) of part `part` when the list is split into
 // `parts` contiguous ranges of matrix-core work (a class with z zero axes
-// runs 1 / 2^z of the row-tile / k-step products), the first holding
-// kSymFirstPart % of it and the others equal shares of the rest: a class
-// belongs to the part that holds the midpoint of its weight.  Lane c handles
-// class c.
+// runs 1 / 2^z of the row-tile / k-step products): of two parts the first holds
+// kSymFirstPart % of it, more parts hold equal shares.  A class belongs to the
+// part that holds the midpoint of its weight.  Lane c handles class c.
 __device__ inline void sym_select_classes(unsigned long long used, const int *rep, int parts, int part, int lane,
                                           int *list, int *zend, int *qa, int *qb)
 {
@@ -402,11 +415,8 @@ __device__ inline void sym_select_classes(unsigned long long used, const int *re
     const unsigned long long b0 = __ballot(u && pz == 0), b1 = __ballot(u && pz == 1), b2 = __ballot(u && pz == 2);
     const int W = 4 * __popcll(b0) + 2 * __popcll(b1) + __popcll(b2);
     const int cw = 4 * __popcll(b0 & below) + 2 * __popcll(b1 & below) + __popcll(b2 & below);
-    // part 0 ends at kSymFirstPart % of the weight, the others share the rest
-    int pt = 0;
-    for (int q = 0; q + 1 < parts; ++q)
-        pt += (int64_t)(2 * cw + w) * 100 * (parts - 1) >=
-              (int64_t)2 * W * (kSymFirstPart * (parts - 1) + q * (100 - kSymFirstPart));
+    const int pt = parts == 2 ? (2 * cw + w) * 100 >= 2 * W * kSymFirstPart
+                              : W > 0 ? min((2 * cw + w) * parts / (2 * W), parts - 1) : 0;
     const unsigned long long lo = __ballot(u && pt < part), hi = __ballot(u && pt <= part);
     if (lane == 0) {
         *qa = __popcll(lo);
@@ -710,14 +720,25 @@ __global__ __launch_bounds__(256, 2) void k_m2l_sym(const PlanView *V, Bases B)
     run_mask(std::integral_constant<int, 5>{});
     run_mask(std::integral_constant<int, 6>{}); // at most two zero axes
     if (tgt < 0) return;
-    static_assert(sym_parts_add(P), "parts add into the zeroed rows");
-    double *Lh = v.Lh + (int64_t)tgt * v.ldh;
+    if (m2l_parts_add(P, parts)) { // into the zeroed rows
+        double *Lh = v.Lh + (int64_t)tgt * v.ldh;
+#pragma unroll
+        for (int mt = 0; mt < MTW; ++mt) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int b = gptr(tb.srow)[16 * mt + Mfma<T>::row(lane, r)];
+                if (b >= 0) atomicAdd(Lh + b, sizeof(T) == 4 ? acc64[mt][r] : (double)acc[mt][r]);
+            }
+        }
+        return;
+    }
+    double *Lh = (part ? v.Lh2 + (int64_t)(part - 1) * v.nboxes * v.ldh : v.Lh) + (int64_t)tgt * v.ldh;
 #pragma unroll
     for (int mt = 0; mt < MTW; ++mt) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int b = gptr(tb.srow)[16 * mt + Mfma<T>::row(lane, r)];
-            if (b >= 0) atomicAdd(Lh + b, sizeof(T) == 4 ? acc64[mt][r] : (double)acc[mt][r]);
+            if (b >= 0) Lh[b] = sizeof(T) == 4 ? acc64[mt][r] : (double)acc[mt][r];
         }
     }
 }
@@ -984,7 +1005,7 @@ __global__ __launch_bounds__(256, 1) void k_m2l_symh(const PlanView *V, Bases B)
     run_mask(std::integral_constant<int, 5>{});
     run_mask(std::integral_constant<int, 6>{});
     if (tgt < 0) return;
-    static_assert(!sym_parts_add(P), "parts store their sums");
+    static_assert(!m2l_parts_add(P, 2), "parts store their sums");
     double *Lh = (part ? v.Lh2 + (int64_t)(part - 1) * v.nboxes * v.ldh : v.Lh) + (int64_t)tgt * v.ldh;
 #pragma unroll
     for (int mt = 0; mt < F32T; ++mt) {

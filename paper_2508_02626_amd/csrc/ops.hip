@@ -435,10 +435,10 @@ __global__ __launch_bounds__(512) void k_l2lh(const PlanView *V, Bases B, int le
     }
 }
 
-// Before the L2L, plans whose M2L stores its rows (orders below 6 and from 12
-// on): Lh rows of boxes (level >= 2) without M2L or P2L contributions are set
-// to zero, and from order 12 the partial sums of the other M2L class parts
-// (Lh2 slices) are added in part order.
+// Before the L2L, plans whose M2L stores its rows (all but m2l_parts_add):
+// Lh rows of boxes (level >= 2) without M2L or P2L contributions are set to
+// zero, and the partial sums of the M2L parts after the first (Lh2 slices) are
+// added in part order.
 __global__ __launch_bounds__(256) void k_lh_init(const PlanView *V, Bases B)
 {
     const int k = find_plan(B, blockIdx.x);
@@ -454,13 +454,20 @@ __global__ __launch_bounds__(256) void k_lh_init(const PlanView *V, Bases B)
         const auto Lh2 = gptr(v.Lh2 + (int64_t)box * v.ldh);
         for (int a = lane; a < v.ldh; a += 64) {
             double s = Lh[a];
-            for (int i = 0; i < v.m2l_parts - 1; ++i) s += Lh2[i * slice + a];
+            const int np = v.m2l_parts - 1;
+            int i = 0;
+            for (; i + 4 <= np; i += 4) { // (four loads in flight, added in order)
+                const double t0 = Lh2[i * slice + a], t1 = Lh2[(i + 1) * slice + a];
+                const double t2 = Lh2[(i + 2) * slice + a], t3 = Lh2[(i + 3) * slice + a];
+                s += t0; s += t1; s += t2; s += t3;
+            }
+            for (; i < np; ++i) s += Lh2[i * slice + a];
             Lh[a] = s;
         }
     }
 }
 
-// Plans whose M2L parts add into Lh (orders 6-11): every row zeroed before
+// Plans whose M2L parts add into Lh (m2l_parts_add): every row zeroed before
 // the M2L (two doubles per thread).
 __global__ __launch_bounds__(256) void k_lh_zero(const PlanView *V, Bases B)
 {
