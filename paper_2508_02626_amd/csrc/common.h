@@ -105,6 +105,12 @@ __host__ __device__ constexpr int sym_row_tiles(int p)
     for (int c = 0; c < 8; ++c) n += (sym_class_count(p, c) + 15) / 16;
     return n;
 }
+__host__ __device__ constexpr int sym_row_pairs(int p) // row tiles of the classes (x, y, 0)
+{
+    int n = 0;
+    for (int c = 0; c < 8; c += 2) n += (sym_class_count(p, c) + 15) / 16;
+    return n;
+}
 // columns of a parity class are padded to a multiple of sym_colpad: 4 (one
 // k-step) at every order; from p = 12 the kernel's 16-byte operand vectors
 // (two k-steps) may hold the last k-step of one class and the first of the

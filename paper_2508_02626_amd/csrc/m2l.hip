@@ -366,10 +366,16 @@ __global__ __launch_bounds__(256) void k_m2l(const PlanView *V, Bases B)
 // k_m2l_symh (orders >= 12) part i > 0 writes its partial sums to slice i - 1 of
 // Lh2, which the pass before the L2L adds in part order.
 template <int P> struct SymShape {
-    static constexpr int RT = sym_row_tiles(P), KS = sym_ksteps(P);
+    static constexpr int RT = sym_row_tiles(P), KS = sym_ksteps(P), RP = sym_row_pairs(P);
     int rc[RT], kc[KS]; // parity class of each row tile and k-step
     int kb[9];          // first k-step of each column class
-    constexpr SymShape() : rc(), kc(), kb()
+    uint64_t tau[3][2]; // bit ks of tau[b]: bit b of k-step ks's class
+    // pairs of row tiles: tile t of parity class (x, y, 0) and tile t of
+    // (x, y, 1), numbered in the order of the z = 0 tiles.  The (i, j, 1) rows of
+    // a class, in increasing degree, have the (i, j) of the first (i, j, 0)
+    // rows, so the D addresses of a pair differ by the z stride alone
+    int pt[RP], pr[RT]; // z = 0 tile of a pair, pair of a row tile
+    constexpr SymShape() : rc(), kc(), kb(), tau(), pt(), pr()
     {
         for (int r = 0; r < RT; ++r) rc[r] = sym_tile_class(P, r, true);
         int k = 0;
@@ -378,21 +384,53 @@ template <int P> struct SymShape {
             for (int t = 0; t < sym_class_ksteps(P, c); ++t) kc[k++] = c;
         }
         kb[8] = k;
+        for (int ks = 0; ks < KS; ++ks)
+            for (int b = 0; b < 3; ++b) tau[b][ks / 64] |= (uint64_t)((kc[ks] >> b) & 1) << (ks % 64);
+        int tn[RT] = {}, q = 0;
+        for (int r = 0; r < RT; ++r) {
+            tn[r] = sym_tile_class(P, r, false);
+            if (!(rc[r] & 1)) pt[q++] = r;
+        }
+        for (int r = 0; r < RT; ++r)
+            for (int i = 0; i < RP; ++i)
+                if ((rc[r] | 1) == (rc[pt[i]] | 1) && tn[r] == tn[pt[i]]) pr[r] = i;
     }
 };
-
-template <typename T> __device__ inline void wht8(T (&h)[8])
-{
-#pragma unroll
-    for (int bit = 1; bit < 8; bit <<= 1)
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-            if (!(i & bit)) {
-                const T u = h[i], w = h[i | bit];
-                h[i] = u + w;
-                h[i | bit] = u - w;
-            }
-}
+template <int P> constexpr SymShape<P> kSymShape{}; // (evaluated once)
+// For zero axes Z: the row tiles whose products with a column class of value
+// GV = tau & Z exist, ordered by pair, with their pairs, and the groups of
+// k-steps: gk is tau & Z of a k-step (-1 past the last), uniform_vectors(j) the
+// number of vectors (two k-steps) from j on whose k-steps and the one after
+// them have the value of k-step 2j.
+template <int P, int Z, int GV> struct SymTiles {
+    int n, t[sym_row_tiles(P)], p[sym_row_tiles(P)];
+    bool used[sym_row_pairs(P)];
+    constexpr SymTiles() : n(0), t(), p(), used()
+    {
+        constexpr const SymShape<P> &S = kSymShape<P>;
+        for (int q = 0; q < S.RP; ++q)
+            for (int r = 0; r < S.RT; ++r)
+                if (S.pr[r] == q && (S.rc[r] & Z) == GV) {
+                    used[q] = true;
+                    p[n] = q;
+                    t[n++] = r;
+                }
+    }
+};
+template <int P, int Z> struct SymGroups {
+    static constexpr int gk(int ks)
+    {
+        constexpr const SymShape<P> &S = kSymShape<P>;
+        return ks < S.KS ? S.kc[ks] & Z : -1;
+    }
+    static constexpr int uniform_vectors(int j)
+    {
+        const int g = gk(2 * j);
+        int n = 0;
+        while (gk(2 * (j + n)) == g && gk(2 * (j + n) + 1) == g && gk(2 * (j + n) + 2) == g) ++n;
+        return n;
+    }
+};
 
 // Run by one whole wavefront: from the mask of classes used by a tile's
 // targets, list them in class order (sList), note where each zero mask's
@@ -429,8 +467,9 @@ __device__ inline void sym_select_classes(unsigned long long used, const int *re
 // that the set-up costs a few memory round trips rather than one per entry.
 // Returns the thread's target (-1 for an empty slot), or kNoTargets when the
 // tile has none (the whole block then returns).  Fills hb (D address of the
-// lane's row in each of the MTW row tiles from R0 on), sTg, sHo (D address of each
-// column), soct and clears sUsed.
+// lane's row in each of the MTW row tiles, or row-tile pairs), sTg, sHo (D
+// address of each column), both in units of UNIT-th entries, soct and clears
+// sUsed.
 constexpr int kNoTargets = -2;
 
 // Tile and part of block i of n = tiles x parts: each XCD gets a contiguous
@@ -451,10 +490,11 @@ __device__ inline void sym_block(int i, int n, int parts, int &tile, int &part)
     tile = rb / parts;
     part = rb - tile * parts;
 }
-template <int MTW, int KS, int R0 = 0>
+template <int P, int MTW, int KS, int LDHO = KS, int UNIT = 1>
 __device__ inline int sym_setup_tile(const PlanView &v, const OrderTables &tb, int tile, int tid, int col, int (&hb)[MTW],
-                                     int *sTg, int (*sHo)[KS], int *soct, unsigned long long *sUsed)
+                                     int *sTg, int (*sHo)[LDHO], int *soct, unsigned long long *sUsed)
 {
+    static constexpr SymShape<P> S{};
     constexpr int NT = 256, NHO = (4 * KS + NT - 1) / NT;
     const auto t_hoff = gptr(tb.hoff), t_srow = gptr(tb.srow), t_scol = gptr(tb.scol);
     const auto mtg = gptr(v.m2l_tgt) + (int64_t)tile * kM2LSlots;
@@ -462,7 +502,7 @@ __device__ inline int sym_setup_tile(const PlanView &v, const OrderTables &tb, i
     const int tgt = mtg[wave * 16 + col], tg64 = mtg[tid & 63];
     int rowi[MTW], coli[NHO];
 #pragma unroll
-    for (int mt = 0; mt < MTW; ++mt) rowi[mt] = t_srow[16 * (R0 + mt) + col];
+    for (int mt = 0; mt < MTW; ++mt) rowi[mt] = t_srow[16 * (MTW == S.RT ? mt : S.pt[mt]) + col];
 #pragma unroll
     for (int i = 0; i < NHO; ++i) {
         const int e = tid + NT * i < 4 * KS ? tid + NT * i : 0, g = e / KS, ks = e - g * KS;
@@ -478,11 +518,11 @@ __device__ inline int sym_setup_tile(const PlanView &v, const OrderTables &tb, i
     if (tid < 64) sTg[tid] = tg64;
     if (tid == 0) *sUsed = 0;
 #pragma unroll
-    for (int mt = 0; mt < MTW; ++mt) hb[mt] = rowi[mt] >= 0 ? hb[mt] : 0;
+    for (int mt = 0; mt < MTW; ++mt) hb[mt] = rowi[mt] >= 0 ? UNIT * hb[mt] : 0;
 #pragma unroll
     for (int i = 0; i < NHO; ++i) {
         const int e = tid + NT * i, g = e / KS, ks = e - g * KS;
-        if (e < 4 * KS) sHo[g][ks] = coli[i] >= 0 ? hov[i] : 0;
+        if (e < 4 * KS) sHo[g][ks] = coli[i] >= 0 ? UNIT * hov[i] : 0;
     }
     if (tgt >= 0) *soct = oct;
     __syncthreads();
@@ -548,7 +588,7 @@ __global__ __launch_bounds__(256, 2) void k_m2l_sym(const PlanView *V, Bases B)
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, col = lane & 15, kq = lane >> 4;
     const OrderTables &tb = *v.tab;
     int hb[MTW];
-    const int tgt = sym_setup_tile<MTW, KS>(v, tb, tile, tid, col, hb, sTg, sHo, &soct, &sUsed);
+    const int tgt = sym_setup_tile<P, MTW, KS>(v, tb, tile, tid, col, hb, sTg, sHo, &soct, &sUsed);
     if (tgt == kNoTargets) return;
     {
         // the targets' slot rows: every load issued before the first is used
@@ -746,18 +786,26 @@ __global__ __launch_bounds__(256, 2) void k_m2l_sym(const PlanView *V, Bases B)
 // ---------------- sign-class M2L for orders >= 12 ----------------
 // The same decomposition as k_m2l_sym (classes in zero-mask order, m2l_parts
 // blocks per tile over parts of the classes, transform of the members, one
-// MFMA per row tile and k-step with a compile-time transform output),
-// organised so that the code stays small at high order: within a class the
-// eight column classes are unrolled while each one's k-steps run in a loop
-// over 16-byte operand vectors (two k-steps; columns are padded to 8 per
-// class so that no vector straddles two classes).  Operands move one vector
-// ahead through a current / next register pair, the next class's first vector
-// loaded during the last one.  The targets' slot rows are read from memory
-// (the classes a block uses come from a 64-bit mask built by all threads),
-// which leaves LDS to the derivative tables.  All row tiles of the 16
-// targets stay in one wavefront (one wavefront per SIMD, the accumulators in
-// the accumulation registers), so that every member operand and transform
-// serves every row.  Row tiles from F32T on (the higher degrees: rows are in
+// MFMA per row tile and k-step), organised so that the code stays small at high
+// order: within a class the k-steps run in loops over 16-byte operand vectors
+// (two k-steps).  The targets' slot rows are read from memory (the classes a
+// block uses come from a 64-bit mask built by all threads), which leaves LDS
+// to the derivative tables.  All row tiles of the 16 targets stay in one
+// wavefront (one wavefront per SIMD, the accumulators in the accumulation
+// registers), so that every member operand and transform serves every row.
+// What bounds it: instruction issue of the one wavefront.  A 16x16x4 FP64 MFMA
+// holds the SIMD's vector unit for its 64 cycles: no vector instruction, of this
+// wavefront or another, runs beside it, and the first one after an MFMA costs
+// 12 cycles, each next one 4 (measured); LDS reads, loads and scalar
+// instructions are free.  So the vector work is kept small (transforms without
+// sign selection, one address per pair of row tiles) and in one block per
+// vector, and everything else is issued between MFMAs.  With the vector work
+// interleaved instead, an MFMA at a time, the launch took 26.8 ms (4e6 Plummer
+// points, p = 14); as the compiler scheduled it, with the reads and their
+// addresses before each k-step, 22.8; in this form 20.1, of which the MFMAs are
+// 14.6.  Reading every member from 16 hot rows, or every table entry from a
+// conflict-free address, changes the time by 2% at most.
+// Row tiles from F32T on (the higher degrees: rows are in
 // sym_tile_class order) run on FP32 MFMA from the same FP64 operands and
 // transform outputs rounded to FP32, each class's FP32 sums added into FP64
 // after the class; a local coefficient of degree n carries about rho^n of the
@@ -768,7 +816,7 @@ __global__ __launch_bounds__(256, 1) void k_m2l_symh(const PlanView *V, Bases B)
     typedef double T;
     static constexpr SymShape<P> S{};
     constexpr int RT = SymShape<P>::RT, KS = SymShape<P>::KS;
-    constexpr int MTW = RT, R0 = 0;
+    constexpr int MTW = RT, RP = sym_row_pairs(P);
     static_assert(MTW <= 24 && F32T >= 1 && F32T <= RT, "row tiles");
     constexpr int N32 = RT - F32T; // FP32 row tiles
     constexpr int KSV = (KS + 1) / 2; // operand vectors per class
@@ -782,7 +830,7 @@ __global__ __launch_bounds__(256, 1) void k_m2l_symh(const PlanView *V, Bases B)
     typedef typename Mfma<float>::acc_t acc32_t;
     typedef T vec_t __attribute__((ext_vector_type(2)));
     __shared__ T sD[2][LDD];
-    __shared__ int sHo[4][KS];
+    __shared__ int sHo[4][KS + 4]; // D byte offset of column (ks, kq); entries past KS are read, not used
     __shared__ int sTg[64];
     __shared__ int sList[kSymClasses];
     __shared__ int sRep[kSymClasses];
@@ -799,8 +847,8 @@ __global__ __launch_bounds__(256, 1) void k_m2l_symh(const PlanView *V, Bases B)
     sym_block(blockIdx.x - B.b[k], B.b[k + 1] - B.b[k], parts, tile, part);
     const int tid = threadIdx.x, lane = tid & 63, col = lane & 15, kq = lane >> 4;
     const OrderTables &tb = *v.tab;
-    int hb[MTW];
-    const int tgt = sym_setup_tile<MTW, KS, R0>(v, tb, tile, tid, col, hb, sTg, sHo, &soct, &sUsed);
+    int hb[RP]; // D byte offset of the lane's row in each pair of row tiles
+    const int tgt = sym_setup_tile<P, RP, KS, KS + 4, 8>(v, tb, tile, tid, col, hb, sTg, sHo, &soct, &sUsed);
     if (tgt == kNoTargets) return;
     const auto vs = gptr(v.vslot);
     {
@@ -869,108 +917,204 @@ __global__ __launch_bounds__(256, 1) void k_m2l_symh(const PlanView *V, Bases B)
     // absent members read the zero row after the boxes
     const uint32_t zoff = (uint32_t)v.nboxes * (uint32_t)ldmh * 8u;
     const uint32_t vrow = (uint32_t)(tgt >= 0 ? tgt : 0) * (uint32_t)kVSlots;
-    auto class_src = [&](int q, uint32_t (&src)[8]) {
+    // (in two steps: the boxes are requested when a class starts and turned
+    // into offsets during its last vector, so no wave waits for them)
+    int mj[8], mb[8];
+    auto member_boxes = [&](int q) {
         const int c = sList[q];
 #pragma unroll
         for (int m = 0; m < 8; ++m) {
-            const int j = sMem[c][m];
-            const int b = j >= 0 && tgt >= 0 ? vs[vrow + (uint32_t)j] : -1;
-            src[m] = (b >= 0 ? (uint32_t)b * (uint32_t)ldmh * 8u : zoff) + 16u * (uint32_t)kq;
+            mj[m] = sMem[c][m];
+            mb[m] = vs[vrow + (uint32_t)max(mj[m], 0)];
+        }
+    };
+    auto member_offsets = [&](uint32_t (&src)[8]) {
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+            asm volatile("" : "+v"(mb[m])); // (waits here)
+            src[m] = ((mb[m] | mj[m] | tgt) >= 0 ? (uint32_t)mb[m] * (uint32_t)ldmh * 8u : zoff) + 16u * (uint32_t)kq;
         }
     };
     const auto Mg = gptr((const char *)Mh);
-    auto load_v = [&](vec_t (&dst)[8], int j, const uint32_t (&src)[8]) {
-#pragma unroll
-        for (int m = 0; m < 8; ++m) {
-            uint32_t o = src[m];
-            asm volatile("" : "+v"(o));
-            dst[m] = *(gp<const vec_t>)(Mg + (uint64_t)o + 64 * j);
-        }
+    // vector j (k-steps 2j, 2j + 1) of the members; members negating a zero
+    // axis of Z are absent and not loaded.  (The empty asm keeps the address a
+    // scalar base plus the member's 32-bit offset, without a copy of it.)
+    vec_t raw[8];
+    auto load_m = [&](int m, int j, uint32_t (&src)[8]) {
+        asm volatile("" : "+v"(src[m]));
+        raw[m] = *(gp<const vec_t>)(Mg + (uint64_t)src[m] + 64 * j);
     };
     uint32_t srcc[8], srcn[8];
-    vec_t cur[8], nxt[8];
 #pragma unroll
     for (int m = 0; m < 8; ++m) srcc[m] = srcn[m] = zoff;
     if (qb > qa) {
         load_d(sList[qa]);
         store_d(0);
-        class_src(qa, srcc);
-        load_v(cur, 0, srcc);
+        member_boxes(qa);
+        member_offsets(srcc);
+#pragma unroll
+        for (int m = 0; m < 8; ++m) load_m(m, 0, srcc);
         __syncthreads();
     }
-    // one class: column classes unrolled, their vectors in a loop.  A column
-    // class may start on the second k-step of a vector (the previous class
-    // ran its first) and end on the first k-step of one (the next class runs
-    // its second): the vector moves on, and the one after it is requested,
-    // where its first k-step is taken.
-    auto run_class = [&](auto zc, const T *D) {
+    // One class.  A vector's vector-unit work (the transforms of its two
+    // k-steps, the LDS addresses of the next two steps' A operands) forms one
+    // block, then its MFMAs run back to back, each followed by the LDS read
+    // that refills its A operand for the following k-step; the next vector's
+    // loads are issued between the two.  (sched_barrier keeps this order.)
+    // K-steps whose column class tau agrees on the zero axes Z (a group: the
+    // same row tiles run) share one code path: the transform output r ^ tau of
+    // a row class r is output r of the transform of the members with
+    // (-1)^|m & tau| folded into the butterflies (u + s w, u - s w, s = +-1 a
+    // scalar; the same roundings), so tau is a run-time value.
+    T h[2][8];  // transforms of the vector's k-steps
+    T ac[MTW];  // A operands of one k-step, in the order of its row tiles
+    uint32_t ho1 = 0, ho2 = 0; // D offsets of k-steps 2j + 1 and 2j + 2
+    auto run_class = [&](auto zc, int curb) {
         constexpr int Z = decltype(zc)::value;
+        typedef SymGroups<P, Z> G;
+        const uint32_t dbase = (uint32_t)curb * (uint32_t)(LDD * sizeof(T));
         const int *Ho = sHo[kq];
-        auto column_class = [&](auto tc) {
-            constexpr int TAU = decltype(tc)::value;
-            constexpr int K0 = S.kb[TAU], K1 = S.kb[TAU + 1];
-            auto kstep = [&](int ks, auto wc) {
-                constexpr int w = decltype(wc)::value;
-                const int ha = Ho[ks];
-                T ac[MTW];
+        auto dread = [&](uint32_t a, int z) { return *(const T *)((const char *)&sD[0][0] + (a + (z ? 8u * dlayout_s2(P) : 0u))); };
+        // scalars +-1 of k-step ks, by axis bit
+        auto sign = [&](int ks, int bit) {
+            uint64_t w = S.tau[bit][0];
+            if constexpr (KS > 64) w = ks >= 64 ? S.tau[bit][1] : w;
+            return __longlong_as_double((long long)(0x3ff0000000000000ull | ((w >> (ks & 63)) << 63)));
+        };
+        auto transform = [&](T (&o)[8], auto wc, const T (&sg)[3]) {
+            constexpr int w = decltype(wc)::value;
 #pragma unroll
-                for (int mt = 0; mt < MTW; ++mt)
-                    if (!((S.rc[mt] ^ TAU) & Z)) ac[mt] = D[hb[mt] + ha];
-                T h[8];
+            for (int m = 0; m < 8; ++m) o[m] = (m & Z) ? T(0) : raw[m][w];
 #pragma unroll
-                for (int m = 0; m < 8; ++m) h[m] = cur[m][w];
-                wht8(h);
+            for (int st = 0; st < 3; ++st)
 #pragma unroll
-                for (int mt = 0; mt < F32T; ++mt)
-                    if (!((S.rc[mt] ^ TAU) & Z))
-                        acc[mt] = Mfma<T>::run(ac[mt], h[S.rc[mt] ^ TAU], acc[mt]);
-                if constexpr (N32 > 0) {
-                    float hf[8];
+                for (int i = 0; i < 8; ++i)
+                    if (!((1 << st) & Z) && !(i & (1 << st)) && !(i & Z)) {
+                        const T u = o[i], x = o[i | (1 << st)];
+                        o[i] = fma(sg[st], x, u);
+                        o[i | (1 << st)] = fma(-sg[st], x, u);
+                    }
+        };
+        T sg[2][3]; // signs of the vector's k-steps
+        // the MFMAs of one k-step (its transform hw, group value GC); refills
+        // the A operands for the k-step of group value GN (-1: none) at the
+        // addresses ad
+        // (side(i): what else is issued after the i-th MFMA)
+        auto products = [&](const T (&hw)[8], auto gcc, auto gnc, const uint32_t *ad, auto side) {
+            constexpr SymTiles<P, Z, decltype(gcc)::value> TC{};
+            constexpr int GN = decltype(gnc)::value;
+            constexpr SymTiles<P, Z, (GN < 0 ? 0 : GN)> TN{};
+            constexpr int nn = GN < 0 ? 0 : TN.n, slots = TC.n > nn ? TC.n : nn;
+            float hf[N32 > 0 ? 8 : 1], af[N32 > 0 ? MTW : 1]; // FP32 tiles' operands
+            if constexpr (N32 > 0) {
 #pragma unroll
-                    for (int m = 0; m < 8; ++m) hf[m] = (float)h[m];
+                for (int m = 0; m < 8; ++m) hf[m] = (float)hw[m];
 #pragma unroll
-                    for (int mt = F32T; mt < MTW; ++mt)
-                        if (!((S.rc[mt] ^ TAU) & Z))
-                            acc32[mt - F32T] = Mfma<float>::run((float)ac[mt], hf[S.rc[mt] ^ TAU], acc32[mt - F32T]);
+                for (int i = 0; i < TC.n; ++i)
+                    if (TC.t[i] >= F32T) af[i] = (float)ac[i];
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int i = 0; i < slots; ++i) {
+                if (i < TC.n) {
+                    const int mt = TC.t[i];
+                    if (mt < F32T) acc[mt] = Mfma<T>::run(ac[i], hw[S.rc[mt] & ~Z], acc[mt]);
+                    else if constexpr (N32 > 0)
+                        acc32[mt - F32T] = Mfma<float>::run(af[i], hf[S.rc[mt] & ~Z], acc32[mt - F32T]);
+                }
+                if (i < nn) ac[i] = dread(ad[TN.p[i]], S.rc[TN.t[i]] & 1);
+                side(i);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        auto addresses = [&](uint32_t (&ad)[RP], uint32_t ho, auto gnc) {
+            constexpr int GN = decltype(gnc)::value;
+            if constexpr (GN >= 0) {
+                constexpr SymTiles<P, Z, GN> TN{};
+#pragma unroll
+                for (int r = 0; r < RP; ++r)
+                    if (TN.used[r]) {
+                        ad[r] = (uint32_t)hb[r] + ho;
+                        asm volatile("" : "+v"(ad[r])); // (the sum is formed here, not at its reads)
+                    }
+            }
+        };
+        // vector j: groups of its k-steps (GB -1: one k-step only) and of the
+        // next vector's first (-1: the class ends); LAST: the last vector of
+        // the class, the next one requested is the next class's first
+        auto vector = [&](int j, auto gac, auto gbc, auto gnc, auto lastc) {
+            constexpr int GB = decltype(gbc)::value;
+            uint32_t ad1[RP], ad2[RP];
+            __builtin_amdgcn_sched_barrier(0);
+            asm volatile("" : "+v"(ho1), "+v"(ho2)); // (waits for the reads here)
+            transform(h[0], std::integral_constant<int, 0>{}, sg[0]);
+            if constexpr (GB >= 0) transform(h[1], std::integral_constant<int, 1>{}, sg[1]);
+            addresses(ad1, ho1 + dbase, gbc);
+            addresses(ad2, ho2 + dbase, gnc);
+            if constexpr (decltype(lastc)::value) member_offsets(srcn);
+            __builtin_amdgcn_sched_barrier(0);
+            constexpr bool LAST = decltype(lastc)::value;
+            constexpr SymTiles<P, Z, decltype(gac)::value> TA{};
+            // the next vector's loads, a few per MFMA, then its signs
+            constexpr int PER = (8 + TA.n - 1) / TA.n;
+            auto fetch = [&](int i) {
+#pragma unroll
+                for (int m = PER * i; m < PER * (i + 1); ++m) {
+                    if (m >= 8) continue;
+                    if constexpr (LAST) load_m(m, 0, srcn);
+                    else if (!(m & Z)) load_m(m, j + 1, srcc);
+                }
+                if (i == 0) {
+                    ho1 = (uint32_t)Ho[2 * j + 3];
+                    ho2 = (uint32_t)Ho[2 * j + 4];
                 }
             };
-            auto request = [&](int j) { // the vector after vector j
-                if (j + 1 < KSV) load_v(nxt, j + 1, srcc);
-                else load_v(nxt, 0, srcn);
-            };
-            auto move_on = [&]() {
-#pragma unroll
-                for (int m = 0; m < 8; ++m) cur[m] = nxt[m];
-            };
-            using W0 = std::integral_constant<int, 0>;
-            using W1 = std::integral_constant<int, 1>;
-            if constexpr (K1 > K0) {
-                if constexpr (K0 % 2 == 1) { // second half of a vector the previous class began
-                    kstep(K0, W1{});
-                    move_on();
+            auto next_signs = [&](int i) {
+                if (i >= 0 && i < 3) {
+                    sg[0][i] = sign(2 * j + 2, i);
+                    sg[1][i] = sign(2 * j + 3, i);
                 }
+            };
+            if constexpr (GB >= 0) {
+                products(h[0], gac, gbc, ad1, fetch);
+                products(h[1], gbc, gnc, ad2, next_signs);
+            } else {
+                products(h[0], gac, gnc, ad2, fetch);
+            }
+        };
+        { // the first k-step's A operands
+            constexpr SymTiles<P, Z, G::gk(0)> T0{};
+            uint32_t ad[RP];
+            addresses(ad, (uint32_t)Ho[0] + dbase, std::integral_constant<int, G::gk(0)>{});
+#pragma unroll
+            for (int i = 0; i < T0.n; ++i) ac[i] = dread(ad[T0.p[i]], S.rc[T0.t[i]] & 1);
+            ho1 = (uint32_t)Ho[1];
+            ho2 = (uint32_t)Ho[2];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                sg[0][i] = sign(0, i);
+                sg[1][i] = sign(1, i);
+            }
+        }
+        // runs of vectors whose k-steps, and the one after, are of one group
+        // in a loop, the others one by one
+        auto run = [&](auto self, auto jc) {
+            constexpr int J = decltype(jc)::value;
+            if constexpr (J < KSV) {
+                constexpr int N = G::uniform_vectors(J); // vectors J .. J + N - 1 alike, none the last
+                using GA = std::integral_constant<int, G::gk(2 * J)>;
+                if constexpr (N > 1) {
 #pragma unroll 1
-                for (int j = (K0 + 1) / 2; j < K1 / 2; ++j) {
-                    request(j);
-                    kstep(2 * j, W0{});
-                    kstep(2 * j + 1, W1{});
-                    move_on();
-                }
-                if constexpr (K1 % 2 == 1) { // first half of a vector
-                    request(K1 / 2);
-                    kstep(K1 - 1, W0{});
-                    if constexpr (K1 == KS) move_on(); // its second half is padding
+                    for (int j = J; j < J + N; ++j) vector(j, GA{}, GA{}, GA{}, std::false_type{});
+                    self(self, std::integral_constant<int, J + N>{});
+                } else {
+                    vector(J, GA{}, std::integral_constant<int, G::gk(2 * J + 1)>{},
+                           std::integral_constant<int, G::gk(2 * J + 2)>{}, std::integral_constant<bool, J == KSV - 1>{});
+                    self(self, std::integral_constant<int, J + 1>{});
                 }
             }
         };
-        column_class(std::integral_constant<int, 0>{});
-        column_class(std::integral_constant<int, 1>{});
-        column_class(std::integral_constant<int, 2>{});
-        column_class(std::integral_constant<int, 3>{});
-        column_class(std::integral_constant<int, 4>{});
-        column_class(std::integral_constant<int, 5>{});
-        column_class(std::integral_constant<int, 6>{});
-        column_class(std::integral_constant<int, 7>{});
+        run(run, std::integral_constant<int, 0>{});
     };
     int q = qa;
     auto run_mask = [&](auto zc) {
@@ -980,9 +1124,9 @@ __global__ __launch_bounds__(256, 1) void k_m2l_symh(const PlanView *V, Bases B)
             const bool more = q + 1 < qb;
             if (more) {
                 load_d(sList[q + 1]);
-                class_src(q + 1, srcn);
+                member_boxes(q + 1);
             }
-            run_class(zc, sD[curb]);
+            run_class(zc, curb);
             if constexpr (N32 > 0) {
 #pragma unroll
                 for (int mt = 0; mt < N32; ++mt) {
