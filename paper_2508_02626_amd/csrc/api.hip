@@ -558,7 +558,9 @@ int build_plan(fmm_plan_s *P, const double *xyz)
     P->nxtgt = (int)Z.nxtgt;
     const int nt = (int)Z.nmtg;
     // ---- phase C: list contents and M2L tiles (sizes known)
-    int64_t slot_cap = ((int64_t)nt + 8 * (kM2LSlots - 1) + kM2LSlots - 1) / kM2LSlots * kM2LSlots;
+    const int by_level = soft && !P->uniform; // (the softened kernel's tables depend on the level)
+    const int tile_groups = 8 * (by_level ? std::max(depth - 1, 1) : 1); // V lists: levels 2..depth
+    int64_t slot_cap = ((int64_t)nt + tile_groups * (kM2LSlots - 1) + kM2LSlots - 1) / kM2LSlots * kM2LSlots;
     if (slot_cap < kM2LSlots) slot_cap = kM2LSlots;
     const int64_t mw = P->nlist[2];
     P->m2l_parts = (P->m2l_rot || soft) ? 1 : m2l_parts_of(P->p, slot_cap / kM2LSlots, nb);
@@ -573,7 +575,7 @@ int build_plan(fmm_plan_s *P, const double *xyz)
         if (!P->reserve(true, o.total)) return fail(FMM_ENOMEM, "device allocation failed (list arrays)");
         Sizer t;
         if (mw > 0) t.add<uint64_t>(mw).add<uint64_t>(mw).add<int32_t>(mw).add<int32_t>(sort_scratch_bytes((int)mw) / 4 + 1);
-        t.add<int>(32).add<uint64_t>(nt + 1).add<uint64_t>(nt + 1).add<int32_t>(nt + 1).add<int32_t>(nt + 1)
+        t.add<int>(kOctOffsetInts).add<uint64_t>(nt + 1).add<uint64_t>(nt + 1).add<int32_t>(nt + 1).add<int32_t>(nt + 1)
          .add<int32_t>(sort_scratch_bytes(nt + 1) / 4 + 1);
         if (!P->reserve(false, t.total)) return fail(FMM_ENOMEM, "device allocation failed (list temporaries)");
     }
@@ -602,12 +604,12 @@ int build_plan(fmm_plan_s *P, const double *xyz)
         fill_i32(P->wsrc, nb, 0, s);
         mark(P->src[2], mw, P->wsrc, s);
     }
-    int *octoff = P->temp<int>(128);
+    int *octoff = P->temp<int>(kOctOffsetInts);
     uint64_t *okey = P->temp<uint64_t>(nt + 1), *otk = P->temp<uint64_t>(nt + 1);
     int32_t *oval = P->temp<int32_t>(nt + 1), *otv = P->temp<int32_t>(nt + 1);
     int32_t *oscr = P->temp<int32_t>(sort_scratch_bytes(nt + 1) / 4 + 1);
     NOMEM(octoff); NOMEM(okey); NOMEM(otk); NOMEM(oval); NOMEM(otv); NOMEM(oscr);
-    m2l_tiles(bx, mtg, nt, P->uniform, okey, oval, otk, otv, oscr, octoff, slots, slot_cap, s);
+    m2l_tiles(bx, mtg, nt, P->uniform, by_level, okey, oval, otk, otv, oscr, octoff, slots, slot_cap, s);
     P->nslots = (int)slot_cap;
 
     PlanView &v = P->view;

@@ -29,13 +29,9 @@
 // A: lane l holds A[l%16][l/16]; B: lane l holds B[l/16][l%16];
 // D: f64 lane l reg r -> D[4r + l/16][l%16], f32 lane l reg r -> D[4(l/16)+r][l%16].
 #include "ops.h"
-
-#include <type_traits>
+#include "sym_engine.h"
 
 namespace fmm {
-
-typedef double double4_t __attribute__((ext_vector_type(4)));
-typedef float float4_t __attribute__((ext_vector_type(4)));
 
 template <typename T> struct Mfma;
 template <> struct Mfma<double> {
@@ -367,6 +363,7 @@ __global__ __launch_bounds__(256) void k_m2l(const PlanView *V, Bases B)
 // Lh2, which the pass before the L2L adds in part order.
 template <int P> struct SymShape {
     static constexpr int RT = sym_row_tiles(P), KS = sym_ksteps(P), RP = sym_row_pairs(P);
+    static constexpr int KSV = (KS + 1) / 2, ZOFF = 8 * dlayout_s2(P); // (sym_engine.h)
     int rc[RT], kc[KS]; // parity class of each row tile and k-step
     int kb[9];          // first k-step of each column class
     uint64_t tau[3][2]; // bit ks of tau[b]: bit b of k-step ks's class
@@ -396,42 +393,6 @@ template <int P> struct SymShape {
                 if ((rc[r] | 1) == (rc[pt[i]] | 1) && tn[r] == tn[pt[i]]) pr[r] = i;
     }
 };
-template <int P> constexpr SymShape<P> kSymShape{}; // (evaluated once)
-// For zero axes Z: the row tiles whose products with a column class of value
-// GV = tau & Z exist, ordered by pair, with their pairs, and the groups of
-// k-steps: gk is tau & Z of a k-step (-1 past the last), uniform_vectors(j) the
-// number of vectors (two k-steps) from j on whose k-steps and the one after
-// them have the value of k-step 2j.
-template <int P, int Z, int GV> struct SymTiles {
-    int n, t[sym_row_tiles(P)], p[sym_row_tiles(P)];
-    bool used[sym_row_pairs(P)];
-    constexpr SymTiles() : n(0), t(), p(), used()
-    {
-        constexpr const SymShape<P> &S = kSymShape<P>;
-        for (int q = 0; q < S.RP; ++q)
-            for (int r = 0; r < S.RT; ++r)
-                if (S.pr[r] == q && (S.rc[r] & Z) == GV) {
-                    used[q] = true;
-                    p[n] = q;
-                    t[n++] = r;
-                }
-    }
-};
-template <int P, int Z> struct SymGroups {
-    static constexpr int gk(int ks)
-    {
-        constexpr const SymShape<P> &S = kSymShape<P>;
-        return ks < S.KS ? S.kc[ks] & Z : -1;
-    }
-    static constexpr int uniform_vectors(int j)
-    {
-        const int g = gk(2 * j);
-        int n = 0;
-        while (gk(2 * (j + n)) == g && gk(2 * (j + n) + 1) == g && gk(2 * (j + n) + 2) == g) ++n;
-        return n;
-    }
-};
-
 // Run by one whole wavefront: from the mask of classes used by a tile's
 // targets, list them in class order (sList), note where each zero mask's
 // classes end in the list (sZend; the table orders classes by zero mask) and
@@ -793,18 +754,7 @@ __global__ __launch_bounds__(256, 2) void k_m2l_sym(const PlanView *V, Bases B)
 // to the derivative tables.  All row tiles of the 16 targets stay in one
 // wavefront (one wavefront per SIMD, the accumulators in the accumulation
 // registers), so that every member operand and transform serves every row.
-// What bounds it: instruction issue of the one wavefront.  A 16x16x4 FP64 MFMA
-// holds the SIMD's vector unit for its 64 cycles: no vector instruction, of this
-// wavefront or another, runs beside it, and the first one after an MFMA costs
-// 12 cycles, each next one 4 (measured); LDS reads, loads and scalar
-// instructions are free.  So the vector work is kept small (transforms without
-// sign selection, one address per pair of row tiles) and in one block per
-// vector, and everything else is issued between MFMAs.  With the vector work
-// interleaved instead, an MFMA at a time, the launch took 26.8 ms (4e6 Plummer
-// points, p = 14); as the compiler scheduled it, with the reads and their
-// addresses before each k-step, 22.8; in this form 20.1, of which the MFMAs are
-// 14.6.  Reading every member from 16 hot rows, or every table entry from a
-// conflict-free address, changes the time by 2% at most.
+// What bounds the inner loop and its form: sym_engine.h.
 // Row tiles from F32T on (the higher degrees: rows are in
 // sym_tile_class order) run on FP32 MFMA from the same FP64 operands and
 // transform outputs rounded to FP32, each class's FP32 sums added into FP64
@@ -819,7 +769,7 @@ __global__ __launch_bounds__(256, 1) void k_m2l_symh(const PlanView *V, Bases B)
     constexpr int MTW = RT, RP = sym_row_pairs(P);
     static_assert(MTW <= 24 && F32T >= 1 && F32T <= RT, "row tiles");
     constexpr int N32 = RT - F32T; // FP32 row tiles
-    constexpr int KSV = (KS + 1) / 2; // operand vectors per class
+    constexpr int KSV = SymShape<P>::KSV; // operand vectors per class
     static_assert(8 * KSV <= folded_ld(P), "two-k-step vectors inside the folded row");
     constexpr int NT = 256;
     constexpr int LDD = dlayout_ldd(P), LDC = dlayout_ldc(P);
@@ -956,166 +906,6 @@ __global__ __launch_bounds__(256, 1) void k_m2l_symh(const PlanView *V, Bases B)
         for (int m = 0; m < 8; ++m) load_m(m, 0, srcc);
         __syncthreads();
     }
-    // One class.  A vector's vector-unit work (the transforms of its two
-    // k-steps, the LDS addresses of the next two steps' A operands) forms one
-    // block, then its MFMAs run back to back, each followed by the LDS read
-    // that refills its A operand for the following k-step; the next vector's
-    // loads are issued between the two.  (sched_barrier keeps this order.)
-    // K-steps whose column class tau agrees on the zero axes Z (a group: the
-    // same row tiles run) share one code path: the transform output r ^ tau of
-    // a row class r is output r of the transform of the members with
-    // (-1)^|m & tau| folded into the butterflies (u + s w, u - s w, s = +-1 a
-    // scalar; the same roundings), so tau is a run-time value.
-    T h[2][8];  // transforms of the vector's k-steps
-    T ac[MTW];  // A operands of one k-step, in the order of its row tiles
-    uint32_t ho1 = 0, ho2 = 0; // D offsets of k-steps 2j + 1 and 2j + 2
-    auto run_class = [&](auto zc, int curb) {
-        constexpr int Z = decltype(zc)::value;
-        typedef SymGroups<P, Z> G;
-        const uint32_t dbase = (uint32_t)curb * (uint32_t)(LDD * sizeof(T));
-        const int *Ho = sHo[kq];
-        auto dread = [&](uint32_t a, int z) { return *(const T *)((const char *)&sD[0][0] + (a + (z ? 8u * dlayout_s2(P) : 0u))); };
-        // scalars +-1 of k-step ks, by axis bit
-        auto sign = [&](int ks, int bit) {
-            uint64_t w = S.tau[bit][0];
-            if constexpr (KS > 64) w = ks >= 64 ? S.tau[bit][1] : w;
-            return __longlong_as_double((long long)(0x3ff0000000000000ull | ((w >> (ks & 63)) << 63)));
-        };
-        auto transform = [&](T (&o)[8], auto wc, const T (&sg)[3]) {
-            constexpr int w = decltype(wc)::value;
-#pragma unroll
-            for (int m = 0; m < 8; ++m) o[m] = (m & Z) ? T(0) : raw[m][w];
-#pragma unroll
-            for (int st = 0; st < 3; ++st)
-#pragma unroll
-                for (int i = 0; i < 8; ++i)
-                    if (!((1 << st) & Z) && !(i & (1 << st)) && !(i & Z)) {
-                        const T u = o[i], x = o[i | (1 << st)];
-                        o[i] = fma(sg[st], x, u);
-                        o[i | (1 << st)] = fma(-sg[st], x, u);
-                    }
-        };
-        T sg[2][3]; // signs of the vector's k-steps
-        // the MFMAs of one k-step (its transform hw, group value GC); refills
-        // the A operands for the k-step of group value GN (-1: none) at the
-        // addresses ad
-        // (side(i): what else is issued after the i-th MFMA)
-        auto products = [&](const T (&hw)[8], auto gcc, auto gnc, const uint32_t *ad, auto side) {
-            constexpr SymTiles<P, Z, decltype(gcc)::value> TC{};
-            constexpr int GN = decltype(gnc)::value;
-            constexpr SymTiles<P, Z, (GN < 0 ? 0 : GN)> TN{};
-            constexpr int nn = GN < 0 ? 0 : TN.n, slots = TC.n > nn ? TC.n : nn;
-            float hf[N32 > 0 ? 8 : 1], af[N32 > 0 ? MTW : 1]; // FP32 tiles' operands
-            if constexpr (N32 > 0) {
-#pragma unroll
-                for (int m = 0; m < 8; ++m) hf[m] = (float)hw[m];
-#pragma unroll
-                for (int i = 0; i < TC.n; ++i)
-                    if (TC.t[i] >= F32T) af[i] = (float)ac[i];
-                __builtin_amdgcn_sched_barrier(0);
-            }
-#pragma unroll
-            for (int i = 0; i < slots; ++i) {
-                if (i < TC.n) {
-                    const int mt = TC.t[i];
-                    if (mt < F32T) acc[mt] = Mfma<T>::run(ac[i], hw[S.rc[mt] & ~Z], acc[mt]);
-                    else if constexpr (N32 > 0)
-                        acc32[mt - F32T] = Mfma<float>::run(af[i], hf[S.rc[mt] & ~Z], acc32[mt - F32T]);
-                }
-                if (i < nn) ac[i] = dread(ad[TN.p[i]], S.rc[TN.t[i]] & 1);
-                side(i);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        };
-        auto addresses = [&](uint32_t (&ad)[RP], uint32_t ho, auto gnc) {
-            constexpr int GN = decltype(gnc)::value;
-            if constexpr (GN >= 0) {
-                constexpr SymTiles<P, Z, GN> TN{};
-#pragma unroll
-                for (int r = 0; r < RP; ++r)
-                    if (TN.used[r]) {
-                        ad[r] = (uint32_t)hb[r] + ho;
-                        asm volatile("" : "+v"(ad[r])); // (the sum is formed here, not at its reads)
-                    }
-            }
-        };
-        // vector j: groups of its k-steps (GB -1: one k-step only) and of the
-        // next vector's first (-1: the class ends); LAST: the last vector of
-        // the class, the next one requested is the next class's first
-        auto vector = [&](int j, auto gac, auto gbc, auto gnc, auto lastc) {
-            constexpr int GB = decltype(gbc)::value;
-            uint32_t ad1[RP], ad2[RP];
-            __builtin_amdgcn_sched_barrier(0);
-            asm volatile("" : "+v"(ho1), "+v"(ho2)); // (waits for the reads here)
-            transform(h[0], std::integral_constant<int, 0>{}, sg[0]);
-            if constexpr (GB >= 0) transform(h[1], std::integral_constant<int, 1>{}, sg[1]);
-            addresses(ad1, ho1 + dbase, gbc);
-            addresses(ad2, ho2 + dbase, gnc);
-            if constexpr (decltype(lastc)::value) member_offsets(srcn);
-            __builtin_amdgcn_sched_barrier(0);
-            constexpr bool LAST = decltype(lastc)::value;
-            constexpr SymTiles<P, Z, decltype(gac)::value> TA{};
-            // the next vector's loads, a few per MFMA, then its signs
-            constexpr int PER = (8 + TA.n - 1) / TA.n;
-            auto fetch = [&](int i) {
-#pragma unroll
-                for (int m = PER * i; m < PER * (i + 1); ++m) {
-                    if (m >= 8) continue;
-                    if constexpr (LAST) load_m(m, 0, srcn);
-                    else if (!(m & Z)) load_m(m, j + 1, srcc);
-                }
-                if (i == 0) {
-                    ho1 = (uint32_t)Ho[2 * j + 3];
-                    ho2 = (uint32_t)Ho[2 * j + 4];
-                }
-            };
-            auto next_signs = [&](int i) {
-                if (i >= 0 && i < 3) {
-                    sg[0][i] = sign(2 * j + 2, i);
-                    sg[1][i] = sign(2 * j + 3, i);
-                }
-            };
-            if constexpr (GB >= 0) {
-                products(h[0], gac, gbc, ad1, fetch);
-                products(h[1], gbc, gnc, ad2, next_signs);
-            } else {
-                products(h[0], gac, gnc, ad2, fetch);
-            }
-        };
-        { // the first k-step's A operands
-            constexpr SymTiles<P, Z, G::gk(0)> T0{};
-            uint32_t ad[RP];
-            addresses(ad, (uint32_t)Ho[0] + dbase, std::integral_constant<int, G::gk(0)>{});
-#pragma unroll
-            for (int i = 0; i < T0.n; ++i) ac[i] = dread(ad[T0.p[i]], S.rc[T0.t[i]] & 1);
-            ho1 = (uint32_t)Ho[1];
-            ho2 = (uint32_t)Ho[2];
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                sg[0][i] = sign(0, i);
-                sg[1][i] = sign(1, i);
-            }
-        }
-        // runs of vectors whose k-steps, and the one after, are of one group
-        // in a loop, the others one by one
-        auto run = [&](auto self, auto jc) {
-            constexpr int J = decltype(jc)::value;
-            if constexpr (J < KSV) {
-                constexpr int N = G::uniform_vectors(J); // vectors J .. J + N - 1 alike, none the last
-                using GA = std::integral_constant<int, G::gk(2 * J)>;
-                if constexpr (N > 1) {
-#pragma unroll 1
-                    for (int j = J; j < J + N; ++j) vector(j, GA{}, GA{}, GA{}, std::false_type{});
-                    self(self, std::integral_constant<int, J + N>{});
-                } else {
-                    vector(J, GA{}, std::integral_constant<int, G::gk(2 * J + 1)>{},
-                           std::integral_constant<int, G::gk(2 * J + 2)>{}, std::integral_constant<bool, J == KSV - 1>{});
-                    self(self, std::integral_constant<int, J + 1>{});
-                }
-            }
-        };
-        run(run, std::integral_constant<int, 0>{});
-    };
     int q = qa;
     auto run_mask = [&](auto zc) {
         const int qend = min(sZend[decltype(zc)::value], qb);
@@ -1126,7 +916,10 @@ __global__ __launch_bounds__(256, 1) void k_m2l_symh(const PlanView *V, Bases B)
                 load_d(sList[q + 1]);
                 member_boxes(q + 1);
             }
-            run_class(zc, curb);
+            sym_run_class<SymShape<P>, decltype(zc)::value, F32T>(
+                (const char *)&sD[0][0], (uint32_t)curb * (uint32_t)(LDD * sizeof(T)), sHo[kq], hb, acc, acc32, raw,
+                [&](int m, int j) { load_m(m, j, srcc); }, [&]() { member_offsets(srcn); },
+                [&](int m) { load_m(m, 0, srcn); });
             if constexpr (N32 > 0) {
 #pragma unroll
                 for (int mt = 0; mt < N32; ++mt) {

@@ -21,15 +21,20 @@ namespace fmm {
 // region the eight octants' tiles are dealt round-robin, so the blocks that
 // run at the same time hold the children of the same parents, whose V lists
 // draw on the same source boxes.
+// by_level (the softened kernel's adaptive trees, whose tables depend on the
+// level): every (octant, level) group starts a tile of its own, so that no tile
+// runs the classes of two levels one after the other (1e6 Plummer points, 64 a
+// leaf: 51 of 944 tiles did, up to three times as long as the others).
 constexpr int kCatBits = 12;
+constexpr int kTileLevels = kMaxDepth + 1;
 
 __global__ __launch_bounds__(256) void k_oct_keys(const BoxArrays bx, const int32_t *tg, int nt, int uniform,
-                                                  uint64_t *key, int32_t *val)
+                                                  int by_level, uint64_t *key, int32_t *val)
 {
     int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= nt) return;
     const int b = tg[i];
-    uint64_t cat = 0;
+    uint64_t cat = by_level ? bx.level[b] : 0;
     if (uniform) {
         const int l = bx.level[b], side = 1 << l;
         int c[3];
@@ -43,47 +48,58 @@ __global__ __launch_bounds__(256) void k_oct_keys(const BoxArrays bx, const int3
     val[i] = b;
 }
 
-// start of every octant in the sorted keys, and the padded output offsets
-__global__ void k_oct_offsets(const uint64_t *key, int nt, int *octoff)
+// The groups (octants, or with by_level octants and levels) in the sorted keys:
+// off.start[o][l] their first targets, off.tile[o][l] their first tiles within
+// the octant's, off.tiles[o] the octant's tiles, off.first[x][o] the first tile
+// of (region x, octant o) in the region-major sequence.
+struct OctOffsets {
+    int start[8][kTileLevels], tile[8][kTileLevels], tiles[8], first[8][8];
+};
+static_assert(sizeof(OctOffsets) <= kOctOffsetInts * sizeof(int), "octant offsets");
+
+__global__ __launch_bounds__(256) void k_oct_offsets(const uint64_t *key, int nt, int by_level, OctOffsets *off)
 {
-    __shared__ int st[9];
-    int o = threadIdx.x;
-    if (o <= 8) {
+    __shared__ int st[8 * kTileLevels + 1];
+    const int nl = by_level ? kTileLevels : 1, ng = 8 * nl, g = threadIdx.x;
+    static_assert(8 * kTileLevels < 256, "one group per thread");
+    if (g <= ng) {
+        const uint64_t k = (uint64_t)(g / nl) << kCatBits | (uint64_t)(g % nl);
         int lo = 0, hi = nt;
         while (lo < hi) {
             int mid = (lo + hi) >> 1;
-            if ((key[mid] >> kCatBits) < (uint64_t)o) lo = mid + 1; else hi = mid;
+            if (key[mid] < k) lo = mid + 1; else hi = mid;
         }
-        st[o] = o == 8 ? nt : lo;
+        st[g] = g == ng ? nt : lo;
     }
     __syncthreads();
-    if (o == 0) {
-        int s = 0;
-        for (int k = 0; k < 8; ++k) {
-            octoff[k] = s;              // padded start
-            octoff[9 + k] = st[k];      // unpadded start
-            octoff[96 + k] = (st[k + 1] - st[k] + 63) / 64; // tiles of the octant
-            s += (st[k + 1] - st[k] + 63) & ~63;
+    if (g < 8) { // the octant's tiles
+        int t = 0;
+        for (int l = 0; l < nl; ++l) {
+            off->start[g][l] = st[g * nl + l];
+            off->tile[g][l] = t;
+            t += (st[g * nl + l + 1] - st[g * nl + l] + 63) / 64;
         }
-        octoff[8] = s;
-        octoff[17] = nt;
-        // first tile of (region x, octant k) in the region-major sequence
+        off->tiles[g] = t;
+    }
+    __syncthreads();
+    if (g == 0) {
         int t = 0;
         for (int x = 0; x < 8; ++x)
             for (int k = 0; k < 8; ++k) {
-                const int T = octoff[96 + k];
-                octoff[32 + 8 * x + k] = t;
+                const int T = off->tiles[k];
+                off->first[x][k] = t;
                 t += (x + 1) * T / 8 - x * T / 8;
             }
     }
 }
 
 __global__ __launch_bounds__(256) void k_oct_place(const uint64_t *key, const int32_t *val, int nt,
-                                                   const int *octoff, int32_t *slots)
+                                                   int by_level, const OctOffsets *off, int32_t *slots)
 {
     int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= nt) return;
-    const int o = (int)(key[i] >> kCatBits), j = i - octoff[9 + o], t = j >> 6, T = octoff[96 + o];
+    const int o = (int)(key[i] >> kCatBits), l = by_level ? (int)(key[i] & ((1 << kCatBits) - 1)) : 0;
+    const int j = i - off->start[o][l], t = off->tile[o][l] + (j >> 6), T = off->tiles[o];
     int x = 0;
     while (x < 7 && t >= (x + 1) * T / 8) ++x;
     // within region x the octants' tiles are dealt round-robin: tile u of
@@ -91,23 +107,24 @@ __global__ __launch_bounds__(256) void k_oct_place(const uint64_t *key, const in
     const int u = t - x * T / 8;
     int pos = 0;
     for (int k = 0; k < 8; ++k) {
-        const int n = (x + 1) * octoff[96 + k] / 8 - x * octoff[96 + k] / 8; // tiles of octant k in region x
+        const int n = (x + 1) * off->tiles[k] / 8 - x * off->tiles[k] / 8; // tiles of octant k in region x
         pos += min(n, u + (k < o ? 1 : 0));
     }
-    const int tile = octoff[32 + 8 * x] + pos;
+    const int tile = off->first[x][0] + pos;
     slots[(int64_t)tile * 64 + (j & 63)] = val[i];
 }
 
-void m2l_tiles(const BoxArrays &bx, const int32_t *tg, int nt, int uniform, uint64_t *key, int32_t *val,
+void m2l_tiles(const BoxArrays &bx, const int32_t *tg, int nt, int uniform, int by_level, uint64_t *key, int32_t *val,
                uint64_t *tk, int32_t *tv, int32_t *sort_scratch, int *octoff, int32_t *slots,
                int64_t slot_cap, hipStream_t s)
 {
     fill_i32(slots, slot_cap, -1, s);
     if (nt == 0) return;
-    k_oct_keys<<<ceil_div(nt, 256), 256, 0, s>>>(bx, tg, nt, uniform, key, val);
+    k_oct_keys<<<ceil_div(nt, 256), 256, 0, s>>>(bx, tg, nt, uniform, by_level, key, val);
     radix_sort_pairs(key, val, tk, tv, nt, kCatBits + 3, sort_scratch, s);
-    k_oct_offsets<<<1, 64, 0, s>>>(key, nt, octoff);
-    k_oct_place<<<ceil_div(nt, 256), 256, 0, s>>>(key, val, nt, octoff, slots);
+    OctOffsets *off = (OctOffsets *)octoff;
+    k_oct_offsets<<<1, 256, 0, s>>>(key, nt, by_level, off);
+    k_oct_place<<<ceil_div(nt, 256), 256, 0, s>>>(key, val, nt, by_level, off, slots);
 }
 
 } // namespace fmm

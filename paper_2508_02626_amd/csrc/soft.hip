@@ -22,10 +22,10 @@
 // a_g = d^g K / g! (degree n = |g|; eta = 0 gives the 1/r recurrence).
 #include "ops.h"
 #include "soft.h"
+#include "sym_engine.h"
 
 namespace fmm {
 
-typedef double double4_t __attribute__((ext_vector_type(4)));
 template <typename T> __device__ inline T gload(const T *p) { return *gptr(p); }
 
 // exponents of the monomial at DA index e of degree n (mono_index inverse)
@@ -324,19 +324,22 @@ __device__ inline void soft_tile_targets(const PlanView &v, const SoftGrid &G, i
 // range and octant (info[1] < 0: no target).  sTg must be visible to the block.
 __device__ inline void soft_tile_levels(const PlanView &v, int tid, const int *sTg, int *sLv, int *info)
 {
-    if (tid < 64) sLv[tid] = sTg[tid] >= 0 ? v.level[sTg[tid]] : -1;
-    __syncthreads();
-    if (tid == 0) {
-        int lo = 1 << 30, hi = -1, oc = 0;
-        for (int q = 0; q < 64; ++q)
-            if (sTg[q] >= 0) {
-                lo = min(lo, sLv[q]);
-                hi = max(hi, sLv[q]);
-                oc = (int)(v.morton[sTg[q]] & 7);
-            }
-        info[0] = lo;
-        info[1] = hi;
-        info[2] = oc;
+    if (tid < 64) { // (one wavefront, a target per lane)
+        const int g = sTg[tid];
+        const int lv = g >= 0 ? v.level[g] : -1, oc = g >= 0 ? (int)(v.morton[g] & 7) : 0;
+        sLv[tid] = lv;
+        int lo = g >= 0 ? lv : 1 << 30, hi = lv;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            lo = min(lo, __shfl_xor(lo, o));
+            hi = max(hi, __shfl_xor(hi, o));
+        }
+        const unsigned long long have = __ballot(g >= 0);
+        if (tid == (have ? __ffsll(have) - 1 : 0)) {
+            info[0] = lo;
+            info[1] = hi;
+            info[2] = oc;
+        }
     }
     __syncthreads();
 }
@@ -528,7 +531,17 @@ template <int P> struct SoftSym {
     }
     static constexpr int NP = ncoef(P), MT = sum_tiles(16), KS = sum_tiles(4), KSV = (KS + 1) / 2, LDMS = 8 * KSV;
     static constexpr int CMAX = csize(0); // the all-even class is the largest
+    // (sym_engine.h; z is the unit stride of the LDS tables)
+    static constexpr int pairs()
+    {
+        int t = 0;
+        for (int c = 0; c < 8; c += 2) t += (csize(c) + 15) / 16;
+        return t;
+    }
+    static constexpr int RT = MT, RP = pairs(), ZOFF = 8;
     int csz[8] = {}, rc[MT] = {}, kc[KS] = {}, rfirst[9] = {}, kfirst[9] = {};
+    uint64_t tau[3][2] = {}; // bit ks of tau[b]: bit b of k-step ks's class
+    int pt[RP] = {}, pr[MT] = {}; // (x, y, 0) tile of a pair, pair of a row tile
     constexpr SoftSym()
     {
         int t = 0, u = 0;
@@ -541,6 +554,14 @@ template <int P> struct SoftSym {
         }
         rfirst[8] = t;
         kfirst[8] = u;
+        for (int ks = 0; ks < KS; ++ks)
+            for (int b = 0; b < 3; ++b) tau[b][ks / 64] |= (uint64_t)((kc[ks] >> b) & 1) << (ks % 64);
+        int np = 0;
+        for (int r = 0; r < MT; ++r)
+            if (!(rc[r] & 1)) pt[np++] = r;
+        for (int r = 0; r < MT; ++r)
+            for (int i = 0; i < RP; ++i)
+                if ((rc[r] | 1) == (rc[pt[i]] | 1) && r - rfirst[rc[r]] == pt[i] - rfirst[rc[pt[i]]]) pr[r] = i;
     }
 };
 int soft_sym_ld(int p)
@@ -552,16 +573,29 @@ int soft_sym_ld(int p)
     }
 }
 
-// pos[c][t]: DA index of the t-th monomial (in DA order) of parity class c
-template <int P, int CMAX, typename IP> __device__ inline void soft_class_positions(IP exps, int tid, int nt, int (*pos)[CMAX])
+// pos[c][t]: DA index of the t-th monomial (in DA order) of parity class c; run
+// by a whole block of 256 threads, one monomial each: its rank is the number of
+// monomials of its class in the lower lanes and wavefronts
+template <int P, int CMAX, typename IP> __device__ inline void soft_class_positions(IP exps, int tid, int (*pos)[CMAX])
 {
-    auto cls = [](int x) { return (x & 1) << 2 | ((x >> 8) & 1) << 1 | ((x >> 16) & 1); };
-    for (int e = tid; e < ncoef(P); e += nt) {
-        const int c = cls(exps[e]);
-        int r = 0;
-        for (int f = 0; f < e; ++f) r += cls(exps[f]) == c;
-        pos[c][r] = e;
+    static_assert(ncoef(P) <= 256, "one monomial per thread");
+    __shared__ int cnt[4][8];
+    const int wave = tid >> 6, lane = tid & 63;
+    const int x = tid < ncoef(P) ? exps[tid] : 0;
+    const int c = tid < ncoef(P) ? (x & 1) << 2 | ((x >> 8) & 1) << 1 | ((x >> 16) & 1) : -1;
+    int r = 0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const unsigned long long m = __ballot(c == k);
+        if (c == k) r = __popcll(m & lanes_below(lane));
+        if (lane == 0) cnt[wave][k] = __popcll(m);
     }
+    __syncthreads();
+    if (c >= 0) {
+        for (int w = 0; w < wave; ++w) r += cnt[w][c];
+        pos[c][r] = tid;
+    }
+    __syncthreads();
 }
 
 // the moments in the sign-class column order; row nrows - 1 is all zero
@@ -575,7 +609,7 @@ __global__ __launch_bounds__(256) void k_soft_msort(const PlanView *V, double *M
     __shared__ int sCol[LDMS];
     const PlanView &v = V[0];
     const int tid = threadIdx.x;
-    soft_class_positions<P, SS::CMAX>(gptr(v.tab->exps), tid, 256, sPos);
+    soft_class_positions<P, SS::CMAX>(gptr(v.tab->exps), tid, sPos);
     __syncthreads();
     for (int q = tid; q < LDMS; q += 256) {
         const int ks = 2 * (q / 8) + (q & 1), g = (q & 7) >> 1;
@@ -595,18 +629,17 @@ __global__ __launch_bounds__(256) void k_soft_msort(const PlanView *V, double *M
     }
 }
 
-// Two blocks of 4 wavefronts per target tile (each block every other class of
-// the tile's used ones), each wavefront 16 targets with all row tiles; per
-// level the classes used by the level's targets, one after the other (in
-// zero-mask order, so Z is a compile-time constant of the loop that runs
-// them; a wavefront skips a class none of its targets has): the
-// representative's table staged in
-// LDS (SoftCube layout, double-buffered), per k-step the 8 members' operands
-// (one 16-byte vector of two k-steps per member, one vector ahead), their
-// transform, then one MFMA per compatible row tile with the output of the
-// transform that the row and column parities select.
+// Two blocks of 4 wavefronts per target tile of one level and octant (each block
+// every other class of the tile's used ones), each wavefront 16 targets with all
+// row tiles: the used classes one after the other in zero-mask order (a wavefront
+// skips a class none of its targets has), the representative's table staged in
+// LDS (SoftCube layout, double-buffered), the products in sym_engine.h's loop.
+// Set-up and class starts issue their loads together or ahead of their use:
+// positions, levels and used classes found one after the other took 0.17 of
+// a block's time.  1e6 Plummer points, p = 8: 6.5 ms before this loop and set-up,
+// 4.3 now; 1e6 uniform points 3.4 -> 2.7.
 template <int P>
-__global__ __launch_bounds__(256) void k_m2l_soft_sym(const PlanView *V, SoftGrid G)
+__global__ __launch_bounds__(256, 1) void k_m2l_soft_sym(const PlanView *V, SoftGrid G)
 {
     using SS = SoftSym<P>;
     static constexpr SS S{};
@@ -616,7 +649,7 @@ __global__ __launch_bounds__(256) void k_m2l_soft_sym(const PlanView *V, SoftGri
     static_assert(8 * CMAX * sizeof(int) <= LDD * sizeof(double), "class positions fit in a table buffer");
     typedef double dvec_t __attribute__((ext_vector_type(2)));
     __shared__ double sD[2][LDD];
-    __shared__ int sHo[4][KS];
+    __shared__ int sHo[4][KS + 4]; // D byte offset of column (ks, kq); entries past KS are read, not used
     __shared__ int sTg[64], sLv[64];
     __shared__ int sRep[kSymClasses];
     __shared__ unsigned char sMem[kSymClasses][8]; // member slots (255: none)
@@ -635,11 +668,11 @@ __global__ __launch_bounds__(256) void k_m2l_soft_sym(const PlanView *V, SoftGri
     // before the M2L (two terms added to zero in either order: deterministic)
     const int item = xcd_remap(blockIdx.x, 2 * G.nblocks), part = item & 1;
     soft_tile_targets(v, G, item >> 1, tid, sTg);
-    soft_class_positions<P, CMAX>(exps, tid, 256, sPos);
+    soft_class_positions<P, CMAX>(exps, tid, sPos);
     __syncthreads();
     soft_tile_levels(v, tid, sTg, sLv, sInfo);
-    const int lmin = sInfo[0], lmax = sInfo[1], oct = sInfo[2];
-    if (lmax < 0) return; // (block-uniform)
+    const int L = sInfo[1], oct = sInfo[2]; // (every tile holds targets of one level)
+    if (L < 0) return; // (block-uniform)
     {
         const auto rep = gptr(tb.srep) + oct * kSymClasses, mem = gptr(tb.smem) + oct * kSymClasses * 8;
         const auto ssl = gptr(tb.sslot) + oct * kVSlots;
@@ -651,16 +684,16 @@ __global__ __launch_bounds__(256) void k_m2l_soft_sym(const PlanView *V, SoftGri
         if (tid < kVSlots) sSl[tid] = (unsigned char)ssl[tid];
         for (int e = tid; e < 4 * KS; e += 256) {
             const int g = e / KS, ks = e - g * KS, c = S.kc[ks], t = 4 * (ks - S.kfirst[c]) + g;
-            sHo[g][ks] = t < S.csz[c] ? SoftCube<P>::addr(exps[sPos[c][t]]) : 0;
+            sHo[g][ks] = t < S.csz[c] ? 8 * SoftCube<P>::addr(exps[sPos[c][t]]) : 0;
         }
     }
-    int hb[MT];
+    int hb[SS::RP]; // D byte offset of the lane's row in each pair of row tiles
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-        const int c = S.rc[mt], t = 16 * (mt - S.rfirst[c]) + col;
-        hb[mt] = t < S.csz[c] ? SoftCube<P>::addr(exps[sPos[c][t]]) : 0;
+    for (int r = 0; r < SS::RP; ++r) {
+        const int c = S.rc[S.pt[r]], t = 16 * (S.pt[r] - S.rfirst[c]) + col;
+        hb[r] = t < S.csz[c] ? 8 * SoftCube<P>::addr(exps[sPos[c][t]]) : 0;
     }
-    const int tgt = sTg[wave * 16 + col], tlev = sLv[wave * 16 + col];
+    const int tgt = sTg[wave * 16 + col];
     const auto vs = gptr(v.vslot);
     const uint32_t zoff = (uint32_t)v.nboxes * (uint32_t)LDMS * 8u; // the all-zero row
     const auto Mg = gptr((const char *)v.Mh);
@@ -674,143 +707,137 @@ __global__ __launch_bounds__(256) void k_m2l_soft_sym(const PlanView *V, SoftGri
             dm[r][w] = e < LDC ? gptr(v.soft_map)[e] : LDD - 1;
         }
     double4_t acc[MT];
+    float4_t none[1]; // (no FP32 tiles)
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) acc[mt] = double4_t{0, 0, 0, 0};
     __syncthreads(); // sPos is overwritten by the tables from here on
 
-    for (int L = lmin; L <= lmax; ++L) {
-        // classes used by the targets of level L
-        if (tid == 0) sUsed = 0;
-        __syncthreads();
-        {
-            unsigned long long used = 0;
-            for (int e = tid; e < 64 * kVSlots; e += 256) {
-                const int q = e / kVSlots, j = e - q * kVSlots;
-                if (sLv[q] == L && vs[(int64_t)sTg[q] * kVSlots + j] >= 0) used |= 1ull << sSl[j];
+    // classes used by the targets
+    if (tid == 0) sUsed = 0;
+    __syncthreads();
+    {
+        unsigned long long used = 0;
+        constexpr int NE = 64 * kVSlots, CH = 16; // (CH loads in flight)
+        for (int e0 = tid; e0 < NE; e0 += 256 * CH) {
+            int val[CH];
+#pragma unroll
+            for (int i = 0; i < CH; ++i) {
+                const int e = min(e0 + 256 * i, NE - 1), q = e / kVSlots, j = e - q * kVSlots;
+                val[i] = vs[(int64_t)max(sTg[q], 0) * kVSlots + j];
             }
-            if (used) atomicOr(&sUsed, used);
+#pragma unroll
+            for (int i = 0; i < CH; ++i) {
+                const int e = min(e0 + 256 * i, NE - 1), q = e / kVSlots, j = e - q * kVSlots;
+                if (sTg[q] >= 0 && val[i] >= 0) used |= 1ull << sSl[j];
+            }
         }
-        __syncthreads();
-        if (tid < 64) { // this part's classes in table order; where each zero mask's classes end
-            const unsigned long long below = lanes_below(lane);
-            const int c = lane;
-            const unsigned long long used =
-                __ballot(c < kSymClasses && ((sUsed >> c) & 1) && (__popcll(sUsed & below) & 1) == part);
-            if (c < kSymClasses && ((used >> c) & 1)) sList[__popcll(used & below)] = (unsigned char)c;
-            const int z = c < kSymClasses ? sRep[c] >> 16 : 0, zn = c + 1 < kSymClasses ? sRep[c + 1] >> 16 : 8;
-            if (c < kSymClasses && zn != z) sZend[z] = __popcll(used & (below | (1ull << c)));
-            if (lane == 0) sN = __popcll(used);
-        }
-        __syncthreads();
-        const int nq = sN;
-        if (nq == 0) continue; // (block-uniform)
-        const double *Dl = v.Dsoft + (int64_t)(L - 2) * 343 * LDC;
-        auto load_d = [&](int c) {
-            const dvec_t *Dk = (const dvec_t *)(Dl + (int64_t)(sRep[c] & 0xffff) * LDC);
-#pragma unroll
-            for (int r = 0; r < DV; ++r) {
-                const int e = tid + 256 * r;
-                pd[r] = e < LDC / 2 ? gload(Dk + e) : dvec_t{0, 0};
-            }
-        };
-        auto store_d = [&](int buf) {
-#pragma unroll
-            for (int r = 0; r < DV; ++r)
-                if (tid + 256 * r < LDC / 2)
-#pragma unroll
-                    for (int w = 0; w < 2; ++w) sD[buf][dm[r][w]] = pd[r][w];
-        };
-        // byte offsets of the members' sorted rows (lane group kq's vector 0)
-        auto class_src = [&](int q, uint32_t (&src)[8]) {
-            const int c = sList[q];
-#pragma unroll
-            for (int m = 0; m < 8; ++m) {
-                const int j = sMem[c][m];
-                const int b = j != 255 && tlev == L ? vs[(int64_t)tgt * kVSlots + j] : -1;
-                src[m] = b >= 0 ? ((uint32_t)b * (uint32_t)LDMS + 2u * (uint32_t)kq) * 8u : zoff + 16u * (uint32_t)kq;
-            }
-        };
-        dvec_t cur[8], nxt[8];
-        auto load_v = [&](dvec_t (&dst)[8], const uint32_t (&src)[8], int j, auto zc) {
-            constexpr int Z = decltype(zc)::value;
-#pragma unroll
-            for (int m = 0; m < 8; ++m) {
-                if (m & Z) continue;
-                uint32_t o = src[m];
-                asm volatile("" : "+v"(o)); // (keeps base + 32-bit offset addressing)
-                dst[m] = *(const __attribute__((address_space(1))) dvec_t *)(Mg + (uint64_t)o + 64u * (uint32_t)j);
-            }
-        };
-        uint32_t srcc[8], srcn[8];
-        load_d(sList[0]);
-        store_d(0);
-        class_src(0, srcc);
-        load_v(cur, srcc, 0, std::integral_constant<int, 0>{});
-        __syncthreads();
-        int q = 0;
-        auto run_mask = [&](auto zc) {
-            constexpr int Z = decltype(zc)::value;
-            const int qend = sZend[Z] < nq ? sZend[Z] : nq;
-            for (; q < qend; ++q) {
-                const int buf = q & 1;
-                const bool more = q + 1 < nq;
-                if (more) {
-                    load_d(sList[q + 1]);
-                    class_src(q + 1, srcn);
-                } else {
-#pragma unroll
-                    for (int m = 0; m < 8; ++m) srcn[m] = zoff + 16u * (uint32_t)kq;
-                }
-                // the wavefront skips a class none of its targets has
-                bool has = false;
-#pragma unroll
-                for (int m = 0; m < 8; ++m) has |= srcc[m] != zoff + 16u * (uint32_t)kq;
-                if (__ballot(has)) {
-                    const double *D = sD[buf];
-                    const int *Ho = sHo[kq];
-#pragma unroll
-                    for (int jv = 0; jv < KSV; ++jv) {
-                        if (jv + 1 < KSV) load_v(nxt, srcc, jv + 1, zc);
-                        else load_v(nxt, srcn, 0, std::integral_constant<int, 0>{});
-#pragma unroll
-                        for (int w = 0; w < 2; ++w) {
-                            const int ks = 2 * jv + w;
-                            if (ks < KS) {
-                                const int ha = Ho[ks];
-                                double h[8];
-#pragma unroll
-                                for (int m = 0; m < 8; ++m) h[m] = (m & Z) ? 0.0 : cur[m][w];
-                                wht8z<Z>(h);
-#pragma unroll
-                                for (int mt = 0; mt < MT; ++mt)
-                                    if (!((S.rc[mt] ^ S.kc[ks]) & Z))
-                                        acc[mt] = __builtin_amdgcn_mfma_f64_16x16x4f64(D[hb[mt] + ha], h[S.rc[mt] ^ S.kc[ks]],
-                                                                                       acc[mt], 0, 0, 0);
-                            }
-                        }
-#pragma unroll
-                        for (int m = 0; m < 8; ++m) cur[m] = nxt[m];
-                    }
-                } else {
-                    load_v(cur, srcn, 0, std::integral_constant<int, 0>{});
-                }
-#pragma unroll
-                for (int m = 0; m < 8; ++m) srcc[m] = srcn[m];
-                if (more) store_d(buf ^ 1);
-                __syncthreads();
-            }
-        };
-        run_mask(std::integral_constant<int, 0>{});
-        run_mask(std::integral_constant<int, 1>{});
-        run_mask(std::integral_constant<int, 2>{});
-        run_mask(std::integral_constant<int, 3>{});
-        run_mask(std::integral_constant<int, 4>{});
-        run_mask(std::integral_constant<int, 5>{});
-        run_mask(std::integral_constant<int, 6>{}); // at most two zero axes
+        if (used) atomicOr(&sUsed, used);
     }
+    __syncthreads();
+    if (tid < 64) { // this part's classes in table order; where each zero mask's classes end
+        const unsigned long long below = lanes_below(lane);
+        const int c = lane;
+        const unsigned long long used =
+            __ballot(c < kSymClasses && ((sUsed >> c) & 1) && (__popcll(sUsed & below) & 1) == part);
+        if (c < kSymClasses && ((used >> c) & 1)) sList[__popcll(used & below)] = (unsigned char)c;
+        const int z = c < kSymClasses ? sRep[c] >> 16 : 0, zn = c + 1 < kSymClasses ? sRep[c + 1] >> 16 : 8;
+        if (c < kSymClasses && zn != z) sZend[z] = __popcll(used & (below | (1ull << c)));
+        if (lane == 0) sN = __popcll(used);
+    }
+    __syncthreads();
+    const int nq = sN;
+    if (nq == 0) return; // (block-uniform)
+    const double *Dl = v.Dsoft + (int64_t)(L - 2) * 343 * LDC;
+    auto load_d = [&](int c) {
+        const dvec_t *Dk = (const dvec_t *)(Dl + (int64_t)(sRep[c] & 0xffff) * LDC);
+#pragma unroll
+        for (int r = 0; r < DV; ++r) {
+            const int e = tid + 256 * r;
+            pd[r] = e < LDC / 2 ? gload(Dk + e) : dvec_t{0, 0};
+        }
+    };
+    auto store_d = [&](int buf) {
+#pragma unroll
+        for (int r = 0; r < DV; ++r)
+            if (tid + 256 * r < LDC / 2)
+#pragma unroll
+                for (int w = 0; w < 2; ++w) sD[buf][dm[r][w]] = pd[r][w];
+    };
+    // byte offsets of the members' sorted rows (lane group kq's vector 0), in
+    // two steps: the boxes are requested when a class starts and turned into
+    // offsets during its last vector, so the wave does not wait for them
+    const uint32_t vrow = (uint32_t)max(tgt, 0) * (uint32_t)kVSlots, zro = zoff + 16u * (uint32_t)kq;
+    int mj[8], mb[8];
+    auto member_boxes = [&](int q) {
+        const int c = sList[q];
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+            mj[m] = sMem[c][m] == 255 ? -1 : sMem[c][m];
+            mb[m] = vs[vrow + (uint32_t)max(mj[m], 0)];
+        }
+    };
+    auto member_offsets = [&](uint32_t (&src)[8]) {
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+            asm volatile("" : "+v"(mb[m])); // (waits here)
+            src[m] = (mb[m] | mj[m] | tgt) >= 0 ? ((uint32_t)mb[m] * (uint32_t)LDMS + 2u * (uint32_t)kq) * 8u : zro;
+        }
+    };
+    double2v_t raw[8];
+    auto load_m = [&](int m, int j, uint32_t (&src)[8]) {
+        asm volatile("" : "+v"(src[m])); // (keeps base + 32-bit offset addressing)
+        raw[m] = *(gp<const double2v_t>)(Mg + (uint64_t)src[m] + 64u * (uint32_t)j);
+    };
+    uint32_t srcc[8], srcn[8];
+    load_d(sList[0]);
+    store_d(0);
+    member_boxes(0);
+    member_offsets(srcc);
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+        srcn[m] = zro;
+        load_m(m, 0, srcc);
+    }
+    __syncthreads();
+    int q = 0;
+    auto run_mask = [&](auto zc) {
+        constexpr int Z = decltype(zc)::value;
+        const int qend = sZend[Z] < nq ? sZend[Z] : nq;
+        for (; q < qend; ++q) {
+            const int buf = q & 1;
+            const bool more = q + 1 < nq;
+            const int qn = more ? q + 1 : q; // (after the last class: requested, not used)
+            load_d(sList[qn]);
+            member_boxes(qn);
+            // the wavefront skips a class none of its targets has
+            bool has = false;
+#pragma unroll
+            for (int m = 0; m < 8; ++m) has |= srcc[m] != zro;
+            if (__ballot(has)) {
+                sym_run_class<SS, Z, MT>((const char *)&sD[0][0], (uint32_t)buf * (uint32_t)(LDD * sizeof(double)),
+                                         sHo[kq], hb, acc, none, raw, [&](int m, int j) { load_m(m, j, srcc); },
+                                         [&]() { member_offsets(srcn); }, [&](int m) { load_m(m, 0, srcn); });
+            } else {
+                member_offsets(srcn);
+#pragma unroll
+                for (int m = 0; m < 8; ++m) load_m(m, 0, srcn);
+            }
+#pragma unroll
+            for (int m = 0; m < 8; ++m) srcc[m] = srcn[m];
+            if (more) store_d(buf ^ 1);
+            __syncthreads();
+        }
+    };
+    run_mask(std::integral_constant<int, 0>{});
+    run_mask(std::integral_constant<int, 1>{});
+    run_mask(std::integral_constant<int, 2>{});
+    run_mask(std::integral_constant<int, 3>{});
+    run_mask(std::integral_constant<int, 4>{});
+    run_mask(std::integral_constant<int, 5>{});
+    run_mask(std::integral_constant<int, 6>{}); // at most two zero axes
     // outputs: row 4 r + kq of each tile, back in DA order
     __syncthreads();
-    soft_class_positions<P, CMAX>(exps, tid, 256, sPos);
+    soft_class_positions<P, CMAX>(exps, tid, sPos);
     __syncthreads();
     if (tgt < 0) return;
     double *Lt = v.L + (int64_t)tgt * v.ldm;

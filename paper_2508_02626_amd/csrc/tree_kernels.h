@@ -50,7 +50,9 @@ void flags(const BoxArrays &bx, int nboxes, const int64_t *xcnt, const int64_t *
 void compact(const int64_t *flag, const int64_t *pos, int nboxes, int32_t *out, hipStream_t s);
 void fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s);
 void mark(const int32_t *idx, int64_t n, int32_t *flag, hipStream_t s); // flag[idx[i]] = 1
-void m2l_tiles(const BoxArrays &bx, const int32_t *tg, int nt, int uniform, uint64_t *key, int32_t *val,
+constexpr int kOctOffsetInts = 512; // ints of m2l_tiles' octoff scratch
+// by_level: no tile holds targets of two levels
+void m2l_tiles(const BoxArrays &bx, const int32_t *tg, int nt, int uniform, int by_level, uint64_t *key, int32_t *val,
                uint64_t *tk, int32_t *tv, int32_t *sort_scratch, int *octoff, int32_t *slots,
                int64_t slot_cap, hipStream_t s);
 
