@@ -853,11 +853,35 @@ int nonleaf_groups(const fmm_plan_s *P, int level)
     int c = P->lvl_nonleaf_off[level + 1] - P->lvl_nonleaf_off[level];
     return (int)ceil_div(c, 16);
 }
-// blocks of the folded M2M at a level (16-parent groups x row-tile groups)
+// blocks of the folded M2M and the harmonic L2L at a level (16-parent groups x
+// row tiles per block, or at sign-class orders four wavefronts per block)
 int m2m_blocks(const fmm_plan_s *P, int level)
 {
     const int g = nonleaf_groups(P, level);
+    if (m2l_sym(P->p)) return (int)ceil_div((int64_t)g * m2m_tile_waves(sym_row_tiles(P->p), g), 4);
     return g * m2m_row_split(P->ldmh / 16, g);
+}
+int l2l_blocks(const fmm_plan_s *P, int level)
+{
+    const int g = nonleaf_groups(P, level);
+    if (m2l_sym(P->p)) return (int)ceil_div((int64_t)g * l2l_tile_waves(sym_row_tiles(P->p), g), 4);
+    return g * (P->ldh / 16);
+}
+void m2m(int p, const PlanView *V, const Bases &B, int level, hipStream_t s)
+{
+    if (m2l_sym(p)) launch_m2m_sym(p, V, B, level, s);
+    else launch_m2mh(p, V, B, level, s);
+}
+void l2l(int p, const PlanView *V, const Bases &B, int level, hipStream_t s)
+{
+    if (m2l_sym(p)) launch_l2l_sym(p, V, B, level, s);
+    else launch_l2lh(p, V, B, level, s);
+}
+// boxes whose Lh rows k_lh_init completes before the L2L
+int lh_init_boxes(const fmm_plan_s *P)
+{
+    if (m2l_parts_add(P->p, P->m2l_parts) || P->depth < 2) return 0;
+    return m2l_sym(P->p) ? P->lvl_begin[3] : P->nboxes;
 }
 
 // Brackets a stage with events when the (single) plan has timing on.
@@ -982,7 +1006,7 @@ int run_pipeline(fmm_plan_s *const *P, int count, const PlanView *V, int fld, hi
     // pass stops at level 2; fmm_plan_export_expansions completes it on demand.
     for (auto &r : runs)
         for (int l = maxdepth - 1; l >= 2; --l)
-            launch_m2mh(P[r.first]->p, V + r.first,
+            m2m(P[r.first]->p, V + r.first,
                         sub(r.first, r.second, [l](const fmm_plan_s *p) { return m2m_blocks(p, l); }), l, s);
     // parents' FP32 operands (mixed M2L) and full multipoles (M2P sources)
     for (auto &r : runs) {
@@ -1033,14 +1057,13 @@ int run_pipeline(fmm_plan_s *const *P, int count, const PlanView *V, int fld, hi
     // complete Lh rows of plans whose M2L stores them (zero where nothing
     // arrived, plus the sums of the M2L parts after the first)
     launch_lh_init(V, sub(0, count, [](const fmm_plan_s *p) {
-        return m2l_parts_add(p->p, p->m2l_parts) ? 0 : (int)ceil_div(p->nboxes, 4); }), s);
+        return (int)ceil_div(lh_init_boxes(p), 4); }), s);
     T.end();
     // L2L on the harmonic components, then full local expansions at the leaves
     T.begin(7);
     for (auto &r : runs)
         for (int l = 2; l < maxdepth; ++l)
-            launch_l2lh(P[r.first]->p, V + r.first,
-                        sub(r.first, r.second, [l](const fmm_plan_s *p) { return nonleaf_groups(p, l) * (p->ldh / 16); }), l, s);
+            l2l(P[r.first]->p, V + r.first, sub(r.first, r.second, [l](const fmm_plan_s *p) { return l2l_blocks(p, l); }), l, s);
     T.end();
     T.begin(6);
     for (auto &r : runs)
@@ -1404,7 +1427,7 @@ extern "C" int fmm_plan_export_expansions(fmm_plan_t plan, hipStream_t stream, d
                 continue;
             }
             B.b[1] = m2m_blocks(P, l);
-            launch_m2mh(P->p, P->view_dev, B, l, stream);
+            m2m(P->p, P->view_dev, B, l, stream);
         }
         if (!soft) {
             B.b[1] = (int)ceil_div(P->nboxes, 4);

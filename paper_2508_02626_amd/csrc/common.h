@@ -189,6 +189,7 @@ __host__ __device__ constexpr int sym_tile_class(int p, int r, bool want_class)
             }
     return -1;
 }
+constexpr int kGHSAhead = 12; // operands of the L2L matrix in flight
 // Folded multipoles of sign-class orders are stored so that a lane's
 // operands of vw consecutive k-steps are adjacent (one 16-byte load): sorted
 // column 4 ks + g (k-step ks, lane group g) sits at 4 vw (ks / vw) + vw g +
@@ -310,8 +311,13 @@ struct OrderTables {
     const int *dmap;    // [ldc] additive-layout address of each compact entry
     const int *offs;    // [8][189] packed offsets (kx+3)*49 + (ky+3)*7 + (kz+3)
     const int *hoff;    // [ldh] additive D address of each harmonic index (-1 padding)
+    // translations: orders below the sign-class ones, per child octant,
     const double *GH;   // [8][nh][nh] L2L on the harmonic components, GH[o][a][c] = d Lh'_c / d Lh_a
     const double *TM;   // [8][ldmh][ldmh] M2M on the folded positions, TM[o][a][c] = d Mh'_c / d Mh_a
+    // and sign-class orders, octant 7 alone, in operand order (translate.hip)
+    const double *GHS;  // [row tiles][k-steps][64], and kGHSAhead k-steps more
+    const double *TMS;  // [2 ceil(k-steps / 2) + 1][row tiles][64]
+    const int *rpos;    // [16 row tiles] folded position of each sorted row (-1 padding)
     const double *HR;   // [nh][nc] full harmonic Mhat from the folded (harmonic-order) components, HR[c][b]
     const int *hpos;    // [nh] folded position of each harmonic component
     const int *hposf;   // [nh] same in the FP32 copy

@@ -21,6 +21,20 @@ __host__ __device__ inline int m2m_row_split(int mt, int groups)
     while (2 * r <= mt && mt % (2 * r) == 0 && groups * r < 512) r *= 2;
     return r;
 }
+// Sign-class orders (translate.hip), 4 wavefronts per block.  Wavefronts per
+// 16-parent group: one for all mt row tiles, or one per row tile where the
+// level's groups would leave SIMDs idle (each reads all the children, so from
+// about 64 groups on their traffic costs more than the idle SIMDs).
+void launch_m2m_sym(int p, const PlanView *V, const Bases &B, int level, hipStream_t s);
+void launch_l2l_sym(int p, const PlanView *V, const Bases &B, int level, hipStream_t s);
+__host__ __device__ inline int m2m_tile_waves(int mt, int groups) { return groups <= 64 ? mt : 1; }
+// L2L: the row tiles of a group spread over up to mt wavefronts until the level
+// has about 2048 (two per SIMD)
+__host__ __device__ inline int l2l_tile_waves(int mt, int groups)
+{
+    const int n = groups > 0 ? 2048 / groups : 1;
+    return n < 1 ? 1 : n < mt ? n : mt;
+}
 void launch_parent_mh(const PlanView *V, const Bases &B, int full, hipStream_t s); // 4 boxes/block
 void launch_unfold(int p, const PlanView *V, const Bases &B, int leaves_only, hipStream_t s); // kRemapBoxes boxes/block
 void launch_p2l(int p, const PlanView *V, const Bases &B, hipStream_t s);  // 1 X target/block

@@ -307,7 +307,7 @@ __device__ inline void mfma_rows(const double *A, int lda, int bA, bool aok, con
     }
 }
 
-// ---------------- M2M on the folded components ----------------
+// ---------------- M2M on the folded components (orders below 6) ----------------
 // The far field of a multipole, hence its translation truncated at degree p,
 // depends only on its folded vector: Mh(parent) = sum_o TM_o^t Mh(child_o),
 // TM_o a (folded positions)^2 matrix.  A block takes 16 parents of one level,
@@ -399,7 +399,7 @@ __global__ __launch_bounds__(256) void k_parent_mh(const PlanView *V, Bases B, i
     }
 }
 
-// ---------------- L2L on the harmonic components ----------------
+// ---------------- L2L on the harmonic components (orders below 6) ----------------
 // Lh(child) += GH_o^t Lh(parent): a block computes 16 rows of 16 parents of
 // one level, one wavefront per child octant (16x16x4 FP64 MFMA), and adds the
 // product of octant o to the octant-o children.
@@ -438,13 +438,14 @@ __global__ __launch_bounds__(512) void k_l2lh(const PlanView *V, Bases B, int le
 // Before the L2L, plans whose M2L stores its rows (all but m2l_parts_add):
 // Lh rows of boxes (level >= 2) without M2L or P2L contributions are set to
 // zero, and the partial sums of the M2L parts after the first (Lh2 slices) are
-// added in part order.
+// added in part order.  At sign-class orders the L2L does this for the children
+// it adds to, and only the boxes of level 2 are left (lh_init_boxes).
 __global__ __launch_bounds__(256) void k_lh_init(const PlanView *V, Bases B)
 {
     const int k = find_plan(B, blockIdx.x);
     const PlanView &v = V[k];
     const int box = (blockIdx.x - B.b[k]) * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (box >= v.nboxes || v.level[box] < 2) return;
+    if (box >= v.nboxes || v.level[box] < 2 || (m2l_sym(v.p) && v.level[box] > 2)) return;
     const bool has_v = v.V_off[box + 1] > v.V_off[box], has_x = v.X_off[box + 1] > v.X_off[box];
     const auto Lh = gptr(v.Lh + (int64_t)box * v.ldh);
     if (!has_v && !has_x) {
@@ -1094,6 +1095,15 @@ template <typename T> __global__ void k_zero(T *p, int64_t n)
     default: KERNEL<16, F> __VA_ARGS__; break;                                                    \
     }
 
+// orders below the sign-class ones
+#define DISPATCH_LOW(p, KERNEL, ...)                                                   \
+    switch (p) {                                                                       \
+    case 0: KERNEL<0> __VA_ARGS__; break;  case 1: KERNEL<1> __VA_ARGS__; break;     \
+    case 2: KERNEL<2> __VA_ARGS__; break;  case 3: KERNEL<3> __VA_ARGS__; break;     \
+    case 4: KERNEL<4> __VA_ARGS__; break;  default: KERNEL<5> __VA_ARGS__; break;    \
+    }
+static_assert(m2l_sym(6) && !m2l_sym(5), "dispatch of the translations");
+
 static inline unsigned nblk(const Bases &B) { return (unsigned)B.b[B.n]; }
 
 void launch_permute_q(const PlanView *V, const Bases &B, hipStream_t s)
@@ -1114,7 +1124,7 @@ void launch_unfold(int p, const PlanView *V, const Bases &B, int leaves_only, hi
 }
 void launch_m2mh(int p, const PlanView *V, const Bases &B, int level, hipStream_t s)
 {
-    if (nblk(B)) DISPATCH_P(p, k_m2mh, <<<nblk(B), 512, 0, s>>>(V, B, level));
+    if (nblk(B)) DISPATCH_LOW(p, k_m2mh, <<<nblk(B), 512, 0, s>>>(V, B, level));
 }
 void launch_parent_mh(const PlanView *V, const Bases &B, int full, hipStream_t s)
 {
@@ -1130,7 +1140,7 @@ void launch_lh_init(const PlanView *V, const Bases &B, hipStream_t s)
 }
 void launch_l2lh(int p, const PlanView *V, const Bases &B, int level, hipStream_t s)
 {
-    if (nblk(B)) DISPATCH_P(p, k_l2lh, <<<nblk(B), 512, 0, s>>>(V, B, level));
+    if (nblk(B)) DISPATCH_LOW(p, k_l2lh, <<<nblk(B), 512, 0, s>>>(V, B, level));
 }
 void launch_p2l(int p, const PlanView *V, const Bases &B, hipStream_t s)
 {

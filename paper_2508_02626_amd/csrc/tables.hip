@@ -168,10 +168,10 @@ std::vector<ld> harmonic_projection(const Mono &m, const std::vector<ld> &v, int
 }
 
 struct Built {
-    std::vector<double> D, S, G, GH, TM, HR, P2M, FP2M, P2L, fold_c, unfold_c, inv_fact, inv_w;
+    std::vector<double> D, S, G, GH, TM, GHS, TMS, HR, P2M, FP2M, P2L, fold_c, unfold_c, inv_fact, inv_w;
     std::vector<float> Df;
     std::vector<int> offs, hoff, fold_off, fold_idx, unfold_off, unfold_idx, exps, dmap;
-    std::vector<int> mpos, mposf, hpos, hposf, srow, scol, srep, smem, sslot;
+    std::vector<int> mpos, mposf, hpos, hposf, rpos, srow, scol, srep, smem, sslot;
     int ldd = 0, ldc = 0;
 };
 
@@ -460,6 +460,23 @@ void build_tables(int p, Built &B)
         if (B.mpos[pa] >= 0) B.hpos[B.mpos[pa]] = pa;
         if (B.mposf[pa] >= 0) B.hposf[B.mposf[pa]] = pa;
     }
+    // sign-class orders: the translations of octant 7 in operand order
+    if (m2l_sym(p)) {
+        const int rt = sym_row_tiles(p), ks = sym_ksteps(p), o = 7;
+        B.TMS.assign((size_t)((ks + 1) / 2 * 2 + 1) * rt * 64, 0.0);
+        B.GHS.assign(((size_t)rt * ks + kGHSAhead) * 64, 0.0);
+        for (int t = 0; t < rt; ++t)
+            for (int s = 0; s < ks; ++s)
+                for (int l = 0; l < 64; ++l) {
+                    const int c = B.srow[16 * t + l % 16], a = B.scol[4 * s + l / 16];
+                    if (a < 0 || c < 0) continue;
+                    B.TMS[((size_t)s * rt + t) * 64 + l] = (double)TMh[((size_t)o * nh + a) * nh + c];
+                    B.GHS[((size_t)t * ks + s) * 64 + l] = B.GH[((size_t)o * nh + a) * nh + c];
+                }
+        for (int r = 0; r < 16 * rt; ++r) B.rpos.push_back(B.srow[r] >= 0 ? B.hpos[B.srow[r]] : -1);
+        B.TM.clear();
+        B.GH.clear();
+    }
     // P2M followed by the fold: raw moments -> folded components (harmonic
     // order), FP2M[g][c] = sum over the fold terms (j, w) of c of w P2M[g][j];
     // both keep the degree, so column c only has entries of its degree's moments
@@ -571,6 +588,7 @@ const OrderTables *get_order_tables(int p, const OrderTables **host_copy, std::s
     if (upload(B.D, &t.D, err) || upload(B.Df, &t.Df, err) || upload(B.dmap, &t.dmap, err) ||
         upload(B.offs, &t.offs, err) ||
         upload(B.hoff, &t.hoff, err) || upload(B.GH, &t.GH, err) || upload(B.TM, &t.TM, err) ||
+        upload(B.GHS, &t.GHS, err) || upload(B.TMS, &t.TMS, err) || upload(B.rpos, &t.rpos, err) ||
         upload(B.HR, &t.HR, err) || upload(B.hpos, &t.hpos, err) || upload(B.hposf, &t.hposf, err) ||
         upload(B.FP2M, &t.FP2M, err) ||
         upload(B.P2L, &t.P2L, err) || upload(B.fold_off, &t.fold_off, err) ||
