@@ -842,8 +842,8 @@ StagePlan stage_blocks(const fmm_plan_s *P)
     sp.unfold = (int)ceil_div(P->nboxes, kRemapBoxes);
     sp.far = (int)ceil_div(P->nleaves, 2); // two leaves per block
     const int split = p2p_split(P->nleaves);
-    sp.p2p[0] = (int)ceil_div(split, 4);
-    sp.p2p[1] = (int)ceil_div(P->nleaves - split, 4);
+    sp.p2p[0] = split;
+    sp.p2p[1] = P->nleaves - split;
     return sp;
 }
 
@@ -881,7 +881,7 @@ void l2l(int p, const PlanView *V, const Bases &B, int level, hipStream_t s)
 int lh_init_boxes(const fmm_plan_s *P)
 {
     if (m2l_parts_add(P->p, P->m2l_parts) || P->depth < 2) return 0;
-    return m2l_sym(P->p) ? P->lvl_begin[3] : P->nboxes;
+    return l2l_completes(P->p, P->m2l_parts) ? P->lvl_begin[3] : P->nboxes;
 }
 
 // Brackets a stage with events when the (single) plan has timing on.

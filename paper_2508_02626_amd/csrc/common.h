@@ -161,6 +161,15 @@ __host__ __device__ constexpr int m2l_parts_of(int p, int64_t tiles, int64_t nbo
 // more than that pass takes), every part after the first stores its sums to a
 // slice of its own and the pass before the L2L adds them in part order.
 __host__ __device__ constexpr bool m2l_parts_add(int p, int parts) { return m2l_sym(p) && p <= 11 && parts == 2; }
+// Plans whose L2L completes the children's rows it adds to (the rows of boxes
+// without a V or X list taken as zero, the second part's sums added), so that no
+// pass over the rows precedes it: sign-class orders with one slice of partial
+// sums at most.  More slices (small trees) are added by the pass: beside a
+// level's few wavefronts their loads took 45 us a launch.
+__host__ __device__ constexpr bool l2l_completes(int p, int parts)
+{
+    return m2l_sym(p) && parts <= 2 && !m2l_parts_add(p, parts);
+}
 // share (percent) of a tile's matrix-core work in its first part; the launch
 // runs the first parts before the others (longest first), so that its end is
 // made of the shorter blocks (uniform 10^6 points, p = 8, FP64: about 6%

@@ -46,7 +46,7 @@ void launch_m2p(int p, int fld, const PlanView *V, const Bases &B, hipStream_t s
 __host__ __device__ inline int p2p_split(int nleaves) { return (int)((int64_t)nleaves * 5 / 8) & ~3; }
 // mixed: 0 FP64, 1 FP32 terms, 2 softened kernel (FP64); fld (here, in
 // launch_far and launch_m2p): 0 when no plan of the launch asks for the field
-void launch_p2p(int mixed, int fld, int part, const PlanView *V, const Bases &B, hipStream_t s); // 4 leaves/block
+void launch_p2p(int mixed, int fld, int part, const PlanView *V, const Bases &B, hipStream_t s); // 1 leaf/block
 void launch_zero(double *p, int64_t n, hipStream_t s);
 void launch_zero_f32(float *p, int64_t n, hipStream_t s);
 void launch_m2l(int p, int f32, const PlanView *V, const Bases &B, hipStream_t s); // 64 slots/block

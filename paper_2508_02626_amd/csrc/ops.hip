@@ -438,14 +438,14 @@ __global__ __launch_bounds__(512) void k_l2lh(const PlanView *V, Bases B, int le
 // Before the L2L, plans whose M2L stores its rows (all but m2l_parts_add):
 // Lh rows of boxes (level >= 2) without M2L or P2L contributions are set to
 // zero, and the partial sums of the M2L parts after the first (Lh2 slices) are
-// added in part order.  At sign-class orders the L2L does this for the children
-// it adds to, and only the boxes of level 2 are left (lh_init_boxes).
+// added in part order.  Where the L2L does this for the children it adds to
+// (l2l_completes), only the boxes of level 2 are left.
 __global__ __launch_bounds__(256) void k_lh_init(const PlanView *V, Bases B)
 {
     const int k = find_plan(B, blockIdx.x);
     const PlanView &v = V[k];
     const int box = (blockIdx.x - B.b[k]) * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (box >= v.nboxes || v.level[box] < 2 || (m2l_sym(v.p) && v.level[box] > 2)) return;
+    if (box >= v.nboxes || v.level[box] < 2 || (l2l_completes(v.p, v.m2l_parts) && v.level[box] > 2)) return;
     const bool has_v = v.V_off[box + 1] > v.V_off[box], has_x = v.X_off[box + 1] > v.X_off[box];
     const auto Lh = gptr(v.Lh + (int64_t)box * v.ldh);
     if (!has_v && !has_x) {
@@ -817,19 +817,30 @@ __global__ __launch_bounds__(64) void k_m2p(const PlanView *V, Bases B)
 // ---------------- P2P ----------------
 // The near-field part goes to phi_near / fld_near (sorted order); the far-field
 // kernel adds it and writes the caller's order.
-// Four wavefronts per block, one target leaf each.  A pass takes up to 64
-// targets of the leaf; every lane holds two of them (targets t and t + TPG,
-// TPG = ceil(c/2) for the c targets of the pass), and the 64 / TPG lane groups
-// split every source chunk into contiguous ranges, so that each source read
-// from LDS serves two pairs and few lanes idle.  The group partial sums are
-// combined in a fixed order at the end.  Source chunks (up to 64 particles,
-// taken from consecutive U-list boxes) are staged in LDS as 32-byte records;
-// the next chunk is loaded into registers while the current one is summed.
+// One wavefront per target leaf.  A pass takes up to 64 targets of the leaf;
+// every lane holds two of them (targets t and t + TPG, TPG = ceil(c/2) for the c
+// targets of the pass), and the 64 / TPG lane groups split every chunk of
+// sources into contiguous ranges of one length (the chunk is padded with
+// zero charges), so that each source read from LDS serves two pairs and few
+// lanes idle.  The group partial sums are combined in a fixed order at the end.
+// The U list is read 64 boxes at a time; the prefix sums of their counts turn a
+// position in the stream of their particles into a particle, so that a chunk of
+// kP2PChunk sources, whatever boxes it spans, is one set of loads per lane, staged
+// in LDS as 32-byte records.
+// What bounds it: FP64 issue, 21 instructions and a reciprocal square root per
+// pair and lane (0.57 ms for the 8.2e8 pairs of 1e6 uniform points at depth 5 with
+// every lane busy).  Filling chunks box by box, with the ranges' lengths divided
+// out per chunk and lanes of unequal ranges masked off, took 0.91 ms there and
+// 3.9 ms on 4e6 Plummer points; this form takes 0.81 and 3.3 (with chunks of 64: 0.84
+// and 3.4).
 // FP64: plain sums.  FP32 (mixed precision): pair offsets are formed in FP64
 // and rounded to FP32, the pair terms are FP32 (hardware rsq), and each
 // lane's sums over all its sources are compensated FP32 sums (Kahan: the
 // rounding error of every addition is carried in a second FP32 register and
 // subtracted at the end), taken to FP64 for the combination of the groups.
+// A lane's FP32 sum depends on its order at the level of the pair terms'
+// rounding (1e-8): that path keeps chunks of 64 and adds no padding.
+template <int MIXED> constexpr int kP2PChunk = MIXED == 1 ? 64 : 128;
 struct SrcRec {
     double x, y, z, q;
 };
@@ -867,13 +878,20 @@ __device__ inline double rsqrt_refined(double x)
     const double e = fma(-(x * y), y, 1.0);
     return fma(y, e * fma(e, 0.375, 0.5), y);
 }
+// the same, 0 for x = 0: the refinement of rsq(0) = inf is the default NaN, whose
+// low word is zero, so clearing the high word is enough
+__device__ inline double rsqrt_or_zero(double x)
+{
+    const double y = rsqrt_refined(x);
+    return __hiloint2double(x > 0.0 ? __double2hiint(y) : 0, __double2loint(y));
+}
 
 // KIND 0 (FP64) and 1 (FP32 terms): a pair contributes iff r^2 > 0, which
 // skips j == i (same coordinates) and coincident points alike.  KIND 2 (the
 // softened kernel, FP64): every j != i with r^2 + eps^2 > 0.
 // FLD: the field terms too (phi is the same bits either way).
 template <int MIXED, bool FLD>
-__device__ inline void p2p_range(const SrcT<MIXED> *S, int lo, int hi, Tgt &a, Tgt &b, double eps2)
+__device__ inline void p2p_range(const SrcT<MIXED> *S, int n, Tgt &a, Tgt &b, double eps2)
 {
     if constexpr (MIXED == 2) {
         auto term = [eps2](const SrcRecS &s, Tgt &t) {
@@ -886,7 +904,8 @@ __device__ inline void p2p_range(const SrcT<MIXED> *S, int lo, int hi, Tgt &a, T
                 t.ex = fma(qr3, dx, t.ex); t.ey = fma(qr3, dy, t.ey); t.ez = fma(qr3, dz, t.ez);
             }
         };
-        for (int jj = lo; jj < hi; ++jj) {
+#pragma unroll 2
+        for (int jj = 0; jj < n; ++jj) {
             const SrcRecS s0 = S[jj];
             term(s0, a);
             term(s0, b);
@@ -906,7 +925,8 @@ __device__ inline void p2p_range(const SrcT<MIXED> *S, int lo, int hi, Tgt &a, T
                 kahan_add(t.s[3], t.c[3], qr3 * dz);
             }
         };
-        for (int jj = lo; jj < hi; ++jj) {
+#pragma unroll 2
+        for (int jj = 0; jj < n; ++jj) { // (n differs between the lane groups)
             const SrcRec s0 = S[jj];
             term(s0, a);
             term(s0, b);
@@ -915,14 +935,15 @@ __device__ inline void p2p_range(const SrcT<MIXED> *S, int lo, int hi, Tgt &a, T
         auto term = [](const SrcRec &s, Tgt &t) {
             const double dx = t.x - s.x, dy = t.y - s.y, dz = t.z - s.z;
             const double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
-            const double ri = r2 > 0.0 ? rsqrt_refined(r2) : 0.0;
+            const double ri = rsqrt_or_zero(r2);
             t.phi = fma(s.q, ri, t.phi);
             if constexpr (FLD) {
                 const double qr3 = s.q * ri * (ri * ri);
                 t.ex = fma(qr3, dx, t.ex); t.ey = fma(qr3, dy, t.ey); t.ez = fma(qr3, dz, t.ez);
             }
         };
-        for (int jj = lo; jj < hi; ++jj) {
+#pragma unroll 2
+        for (int jj = 0; jj < n; ++jj) {
             const SrcRec s0 = S[jj];
             term(s0, a);
             term(s0, b);
@@ -930,31 +951,28 @@ __device__ inline void p2p_range(const SrcT<MIXED> *S, int lo, int hi, Tgt &a, T
     }
 }
 
-// five waves per SIMD (at most 102 VGPRs): the kernel waits on its source
-// loads more than on arithmetic, and the few values this spills are read
-// once per target pass, outside the pair loop
+// (one wavefront per block: a block holds its place until its longest leaf ends)
 template <int MIXED, bool FLD>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_p2p(const PlanView *V, Bases B, int part)
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_p2p(const PlanView *V, Bases B, int part)
 {
-    __shared__ SrcT<MIXED> sS[4][64];
     constexpr int NF = FLD ? 4 : 1;      // sums per target
-    __shared__ double sR[4][2 * NF][64]; // group partials for the final combination
+    constexpr int CH = kP2PChunk<MIXED>;
+    __shared__ SrcT<MIXED> S[CH + 64];        // (a chunk and its padding)
+    double(*R)[64] = (double(*)[64])S;        // after the last chunk: group partials for the combination
+    static_assert(sizeof(S) >= 2 * NF * 64 * sizeof(double), "partials in the chunk's place");
+    __shared__ int sPre[64], sOff[64];   // of 64 U-list boxes: particles before each, first particle minus that
     int k = find_plan(B, blockIdx.x);
     const PlanView &v = V[k];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int lane = threadIdx.x;
     // part 0: leaves [0, split), part 1: leaves [split, nleaves)
     const int split = p2p_split(v.nleaves);
-    const int lo = part ? split : 0, hi = part ? v.nleaves : split;
-    const int li = lo + xcd_remap(blockIdx.x - B.b[k], B.b[k + 1] - B.b[k]) * 4 + wave;
-    if (li >= hi) return;
+    const int li = (part ? split : 0) + xcd_remap(blockIdx.x - B.b[k], B.b[k + 1] - B.b[k]);
     const auto first = gptr(v.first), count = gptr(v.count), usrc = gptr(v.U_src);
     const auto xs = gptr(v.xs), ys = gptr(v.ys), zs = gptr(v.zs);
     const auto qs = gptr(v.qs);
     const int box = v.leaves[li];
     const int f = first[box], cnt = count[box];
     const int64_t u0 = v.U_off[box], u1 = v.U_off[box + 1];
-    SrcT<MIXED> *S = sS[wave];
-    double(*R)[64] = sR[wave];
     for (int ts = 0; ts < cnt; ts += 64) {
         const int c = cnt - ts < 64 ? cnt - ts : 64;
         const int TPG = (c + 1) >> 1, G = 64 / TPG, grp = lane / TPG, tl = lane - grp * TPG;
@@ -972,59 +990,53 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
         tb.phi = tb.ex = tb.ey = tb.ez = 0.0;
 #pragma unroll
         for (int r = 0; r < 4; ++r) ta.s[r] = ta.c[r] = tb.s[r] = tb.c[r] = 0.f;
-        // the U list's particles as one stream, in chunks of up to CH (a chunk
-        // spans several source boxes), the next chunk prefetched into registers
-        constexpr int CH = 64;
-        // the U list's boxes are read 64 at a time, lane l holding the first
-        // particle and the count of entry ub + l, so that walking the list
-        // waits on one chain of dependent loads per 64 boxes, not one per box
-        int64_t ub = u0;
-        int bfirst = 0, bcount = 0;
-        auto load_boxes = [&]() {
-            const int64_t ee = ub + lane;
-            bfirst = 0;
-            bcount = 0;
-            if (ee < u1) { const int src = usrc[ee]; bfirst = first[src]; bcount = count[src]; }
-        };
-        int64_t e = u0;
-        int s = 0, sf = 0, sc = 0;
-        auto box_at = [&]() { // sf, sc of entry e (u0 <= e < u1, e - ub <= 64)
-            if (e - ub >= 64) { ub += 64; load_boxes(); }
-            const int l = (int)(e - ub);
-            sf = __builtin_amdgcn_readlane(bfirst, l);
-            sc = __builtin_amdgcn_readlane(bcount, l);
-        };
-        load_boxes();
-        if (e < u1) box_at();
-        SrcT<MIXED> nx{};
-        auto fill = [&]() { // next chunk into nx; returns its size
-            int m = 0;
-            while (m < CH && e < u1) {
-                const int take = sc - s < CH - m ? sc - s : CH - m;
-                if (lane >= m && lane < m + take) {
-                    const int j = sf + s + (lane - m);
-                    nx.x = xs[j]; nx.y = ys[j]; nx.z = zs[j]; nx.q = qs[j];
-                    if constexpr (MIXED == 2) nx.j = j;
-                }
-                m += take;
-                s += take;
-                if (s >= sc) {
-                    s = 0;
-                    if (++e < u1) box_at();
-                }
+        int m = 0; // particles staged
+        for (int64_t ub = u0; ub < u1; ub += 64) {
+            int bf = 0, bc = 0;
+            if (ub + lane < u1) { const int src = usrc[ub + lane]; bf = first[src]; bc = count[src]; }
+            int incl = bc;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int t = __shfl_up(incl, o);
+                if (lane >= o) incl += t;
             }
-            return m;
-        };
-        int m = fill();
-        while (m > 0) {
+            const int total = __builtin_amdgcn_readlane(incl, 63);
             wave_sync();
-            S[lane] = nx;
+            sPre[lane] = incl - bc;
+            sOff[lane] = bf - (incl - bc);
             wave_sync();
-            const int mn = fill(); // in flight during this chunk's pairs
-            const int per = (m + G - 1) / G;
-            const int lo = inG ? grp * per : m, hi = lo + per < m ? lo + per : m;
-            p2p_range<MIXED, FLD>(S, lo, hi, ta, tb, v.eps2);
-            m = mn;
+            const bool last = ub + 64 >= u1;
+            for (int s0 = 0; s0 < total;) {
+                const int take = min(total - s0, CH - m);
+                SrcT<MIXED> rec[CH / 64];
+#pragma unroll
+                for (int h = 0; h < CH / 64; ++h) { // (positions past the end repeat the last particle)
+                    const int p = min(s0 + 64 * h + lane, s0 + take - 1);
+                    int e = 0; // the box holding position p: the last one starting at or before it
+#pragma unroll
+                    for (int st = 32; st > 0; st >>= 1)
+                        if (sPre[e + st] <= p) e += st;
+                    const int j = p + sOff[e];
+                    rec[h].x = xs[j]; rec[h].y = ys[j]; rec[h].z = zs[j]; rec[h].q = qs[j];
+                    if constexpr (MIXED == 2) rec[h].j = j;
+                }
+                // (a chunk that this batch of boxes does not fill is completed by the next one)
+#pragma unroll
+                for (int h = 0; h < CH / 64; ++h)
+                    if (64 * h + lane < take) S[m + 64 * h + lane] = rec[h];
+                m += take;
+                s0 += take;
+                if (m < CH && !(last && s0 == total)) continue;
+                const int per = (m + G - 1) / G, lo = inG ? grp * per : 0; // (per: uniform)
+                if constexpr (MIXED != 1) { // zero charges up to per * G < m + G
+                    rec[0].q = 0.0;
+                    if (lane < G) S[m + lane] = rec[0];
+                }
+                wave_sync();
+                p2p_range<MIXED, FLD>(S + lo, MIXED != 1 ? per : inG ? min(per, m - lo) : 0, ta, tb, v.eps2);
+                wave_sync(); // the chunk is consumed
+                m = 0;
+            }
         }
         if (MIXED == 1) { // compensated FP32 sums -> FP64
             ta.phi = (double)ta.s[0] - (double)ta.c[0]; ta.ex = (double)ta.s[1] - (double)ta.c[1];
@@ -1033,7 +1045,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
             tb.ey = (double)tb.s[2] - (double)tb.c[2]; tb.ez = (double)tb.s[3] - (double)tb.c[3];
         }
         // combine the lane groups in a fixed order
-        wave_sync();
+        wave_sync(); // the last chunk is consumed
         R[0][lane] = ta.phi; R[NF][lane] = tb.phi;
         if constexpr (FLD) {
             R[1][lane] = ta.ex; R[2][lane] = ta.ey; R[3][lane] = ta.ez;
@@ -1060,6 +1072,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
                 }
             }
         }
+        wave_sync(); // the next pass stages its chunks there
     }
 }
 
@@ -1164,9 +1177,9 @@ void launch_far(int p, int fld, const PlanView *V, const Bases &B, hipStream_t s
 }
 template <bool FLD> static void p2p_kind(int mixed, int part, const PlanView *V, const Bases &B, hipStream_t s)
 {
-    if (mixed == 2) k_p2p<2, FLD><<<nblk(B), 256, 0, s>>>(V, B, part);
-    else if (mixed) k_p2p<1, FLD><<<nblk(B), 256, 0, s>>>(V, B, part);
-    else k_p2p<0, FLD><<<nblk(B), 256, 0, s>>>(V, B, part);
+    if (mixed == 2) k_p2p<2, FLD><<<nblk(B), 64, 0, s>>>(V, B, part);
+    else if (mixed) k_p2p<1, FLD><<<nblk(B), 64, 0, s>>>(V, B, part);
+    else k_p2p<0, FLD><<<nblk(B), 64, 0, s>>>(V, B, part);
 }
 void launch_p2p(int mixed, int fld, int part, const PlanView *V, const Bases &B, hipStream_t s)
 {

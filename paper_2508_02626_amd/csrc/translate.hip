@@ -15,7 +15,8 @@
 // parents, the latency of one wavefront's chain.  The eight-matrix kernels
 // they replace read 8 (p+1)^4 entries per 16 parents (3.2 MB at p = 14) and, for
 // the L2L, the parent's vector once per row tile and octant.  4e6 Plummer points,
-// p = 14: @@T.
+// p = 14: M2M 1.84 -> 1.07 ms and the L2L with the pass before it 5.3 -> 4.9 ms beside
+// the P2P (0.6 and 1.6 alone).
 //
 // Matrices are stored in operand order: TMS[ks][tile][lane], GHS[tile][ks][lane],
 // lane (k, c) holding the entry of column 4 ks + k (parity-sorted) and row
@@ -166,7 +167,7 @@ __global__ __launch_bounds__(256) void k_m2m_sym(const PlanView *V, Bases B, int
         return;
     }
     // one row tile
-    constexpr int NB = 3; // vectors in flight
+    constexpr int NB = 6; // vectors in flight
     const uint32_t rho = (uint32_t)S.rc[mt0];
     double srho[8];
 #pragma unroll
@@ -208,9 +209,8 @@ __global__ __launch_bounds__(256) void k_m2m_sym(const PlanView *V, Bases B, int
 // A wavefront takes 16 parents of a level and some of the row tiles
 // (l2l_tile_waves): the parents' vectors stay in registers (one k-step's operand
 // per lane each), each tile accumulates the eight column classes apart, and the
-// transform over them gives the eight children.  The children's rows are
-// completed on the way: the M2L parts after the first are added (Lh2 slices),
-// and rows that nothing has written are taken as zero.
+// transform over them gives the eight children, their rows completed on the way
+// where no pass has done so (l2l_completes).
 template <int P>
 __global__ __launch_bounds__(256) void k_l2l_sym(const PlanView *V, Bases B, int level)
 {
@@ -245,20 +245,18 @@ __global__ __launch_bounds__(256) void k_l2l_sym(const PlanView *V, Bases B, int
     }
     int ch[8];
     children_by_axes(v, parent, ch);
-    // which children's rows hold something: bit m, M2L rows at bit 8 + m
-    const int np = m2l_parts_add(P, v.m2l_parts) ? 0 : v.m2l_parts - 1;
-    uint32_t have = 0;
-    if (m2l_parts_add(P, v.m2l_parts)) {
-        have = 0xffu; // (zeroed before the M2L)
-    } else {
+    // which children's rows hold something (bit m), and a second part's sums
+    // (bit 8 + m)
+    uint32_t have = 0xffu;
+    if (l2l_completes(P, v.m2l_parts)) {
+        have = 0;
 #pragma unroll
         for (int m = 0; m < 8; ++m) {
             const int b = max(ch[m], 0);
             const bool hv = gptr(v.V_off)[b + 1] > gptr(v.V_off)[b], hx = gptr(v.X_off)[b + 1] > gptr(v.X_off)[b];
-            have |= (uint32_t)(hv || hx) << m | (uint32_t)hv << (8 + m);
+            have |= (uint32_t)(hv || hx) << m | (uint32_t)(hv && v.m2l_parts > 1) << (8 + m);
         }
     }
-    const int64_t slice = (int64_t)v.nboxes * LDH;
     const auto Lh = gptr(v.Lh), Lh2 = gptr(v.Lh2);
     for (int t = t0; t < t1; ++t) {
         double4_t z[8];
@@ -300,10 +298,9 @@ __global__ __launch_bounds__(256) void k_l2l_sym(const PlanView *V, Bases B, int
             double old[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) old[r] = (have >> m) & 1 ? row[max(c[r], 0)] : 0.0;
-            if ((have >> (8 + m)) & 1) // (no bit is set where the parts add)
-                for (int i = 0; i < np; ++i)
+            if ((have >> (8 + m)) & 1)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) old[r] += Lh2[i * slice + (int64_t)ch[m] * LDH + max(c[r], 0)];
+                for (int r = 0; r < 4; ++r) old[r] += Lh2[(int64_t)ch[m] * LDH + max(c[r], 0)];
 #pragma unroll
             for (int r = 0; r < 4; ++r)
                 if (c[r] >= 0) row[c[r]] = fma(s, z[m][r], old[r]);
