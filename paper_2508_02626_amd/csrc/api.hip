@@ -404,8 +404,13 @@ int build_plan(fmm_plan_s *P, const double *xyz)
     const bool given = P->root[3] > 0;
     plan_init(given ? P->root : nullptr, root_dev, bad, s);
     if (!given) bbox(xyz, n, part, root_dev, s); // bounding cube, stays on the device
-    morton_keys(xyz, n, root_dev, P->D, keys, P->perm, bad, s);
-    radix_sort_pairs(keys, P->perm, tk, tv, n, 3 * P->D, sscr, s);
+    if (sort_lands_in_tmp(n, 0, 3 * P->D)) { // sorted from the temporaries into (keys, perm)
+        morton_keys(xyz, n, root_dev, P->D, tk, tv, bad, s);
+        radix_sort_pairs(tk, tv, keys, P->perm, n, 0, 3 * P->D, sscr, s);
+    } else {
+        morton_keys(xyz, n, root_dev, P->D, keys, P->perm, bad, s);
+        radix_sort_pairs(keys, P->perm, tk, tv, n, 0, 3 * P->D, sscr, s);
+    }
     gather_sorted(xyz, P->perm, n, xs, ys, zs, s);
     // ---- box count
     int64_t *ecnt = nullptr, *eoff = nullptr;
@@ -534,10 +539,10 @@ int build_plan(fmm_plan_s *P, const double *xyz)
         int64_t *out[8] = {P->off[0], P->off[1], P->off[2], P->off[3], pos[0], pos[1], pos[2], pos[3]};
         scan_exclusive_multi(in, out, 8, nb, mscr, s);
     }
-    compact(flg[0], pos[0], nb, leaves, s);
-    compact(flg[1], pos[1], nb, nonleaf, s);
-    compact(flg[2], pos[2], nb, xtgt, s);
-    compact(flg[3], pos[3], nb, mtg, s);
+    {
+        int32_t *out[4] = {leaves, nonleaf, xtgt, mtg};
+        compact4(flg, pos, nb, out, s);
+    }
     k_collect_sizes<<<1, 64, 0, s>>>(P->off[0], P->off[1], P->off[2], P->off[3], pos[0], pos[1], pos[2], pos[3],
                                      lvl_dev, root_dev, bad, nb, sizes_dev, lnl_off);
     HIPCHK(hipGetLastError());
@@ -594,10 +599,11 @@ int build_plan(fmm_plan_s *P, const double *xyz)
         uint64_t *wk = P->temp<uint64_t>(mw), *wk2 = P->temp<uint64_t>(mw);
         int32_t *wv2 = P->temp<int32_t>(mw), *wscr = P->temp<int32_t>(sort_scratch_bytes((int)mw) / 4 + 1);
         NOMEM(wk); NOMEM(wk2); NOMEM(wv2); NOMEM(wscr);
-        w_pairs(P->off[2], P->src[2], nb, wk, P->src[3], s);
         int bits = 1;
         while ((1LL << bits) < nb) ++bits;
-        radix_sort_pairs(wk, P->src[3], wk2, wv2, (int)mw, bits, wscr, s);
+        const bool tmp = sort_lands_in_tmp((int)mw, 0, bits); // sorted from wv2 into src[3]
+        w_pairs(P->off[2], P->src[2], nb, wk, tmp ? wv2 : P->src[3], s);
+        radix_sort_pairs(wk, tmp ? wv2 : P->src[3], wk2, tmp ? P->src[3] : wv2, (int)mw, 0, bits, wscr, s);
         // M2P sources: their full multipoles are rebuilt from the folded ones
         P->wsrc = P->own<int32_t>(nb);
         NOMEM(P->wsrc);

@@ -121,7 +121,13 @@ void m2l_tiles(const BoxArrays &bx, const int32_t *tg, int nt, int uniform, int 
     fill_i32(slots, slot_cap, -1, s);
     if (nt == 0) return;
     k_oct_keys<<<ceil_div(nt, 256), 256, 0, s>>>(bx, tg, nt, uniform, by_level, key, val);
-    radix_sort_pairs(key, val, tk, tv, nt, kCatBits + 3, sort_scratch, s);
+    // (adaptive Coulomb trees have no category: the octant's digit alone)
+    const int lo = uniform || by_level ? 0 : kCatBits, hi = kCatBits + 3;
+    radix_sort_pairs(key, val, tk, tv, nt, lo, hi, sort_scratch, s);
+    if (sort_lands_in_tmp(nt, lo, hi)) {
+        key = tk;
+        val = tv;
+    }
     OctOffsets *off = (OctOffsets *)octoff;
     k_oct_offsets<<<1, 256, 0, s>>>(key, nt, by_level, off);
     k_oct_place<<<ceil_div(nt, 256), 256, 0, s>>>(key, val, nt, by_level, off, slots);

@@ -12,6 +12,9 @@ size_t scan_multi_scratch_bytes(int64_t n, int count);
 void scan_exclusive_multi(const int64_t *const *in, int64_t *const *out, int count, int64_t n,
                           int64_t *scratch, hipStream_t s);
 size_t sort_scratch_bytes(int n);
-void radix_sort_pairs(uint64_t *keys, int32_t *vals, uint64_t *tk, int32_t *tv, int n, int bits,
+// stable sort by bits [lo, hi) of the keys; the result is in (tk, tv) if
+// sort_lands_in_tmp, else in (keys, vals)
+bool sort_lands_in_tmp(int n, int lo, int hi);
+void radix_sort_pairs(uint64_t *keys, int32_t *vals, uint64_t *tk, int32_t *tv, int n, int lo, int hi,
                       int32_t *scratch, hipStream_t s);
 } // namespace fmm

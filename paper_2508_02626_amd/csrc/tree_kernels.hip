@@ -333,8 +333,9 @@ void adaptive_boxes(const uint64_t *keys, int n, int D, int leaf_size, const int
 {
     k_emit_fill<<<ceil_div(n, 256), 256, 0, s>>>(keys, n, D, leaf_size, off, elevel, eidx, efirst, ecount,
                                                  emorton);
-    radix_sort_pairs(elevel, eidx, tk, tv, nb, 5, sort_scratch, s);
-    k_box_place<<<ceil_div(nb, 256), 256, 0, s>>>(elevel, eidx, nb, efirst, ecount, emorton, bx);
+    radix_sort_pairs(elevel, eidx, tk, tv, nb, 0, 5, sort_scratch, s);
+    const bool tmp = sort_lands_in_tmp(nb, 0, 5);
+    k_box_place<<<ceil_div(nb, 256), 256, 0, s>>>(tmp ? tk : elevel, tmp ? tv : eidx, nb, efirst, ecount, emorton, bx);
     k_level_bounds<<<ceil_div(nb, 256), 256, 0, s>>>(bx.level, nb, lvl_begin);
     k_box_links<<<ceil_div(nb, 256), 256, 0, s>>>(bx, nb, lvl_begin);
 }
@@ -814,17 +815,23 @@ void flags(const BoxArrays &bx, int nboxes, const int64_t *xcnt, const int64_t *
     k_flags<<<ceil_div(nboxes, 256), 256, 0, s>>>(bx, nboxes, xcnt, vcnt, fleaf, fnon, fx, fv);
 }
 
-__global__ __launch_bounds__(256) void k_compact(const int64_t *flag, const int64_t *pos, int nboxes,
-                                                 int32_t *out)
+struct CompactBatch {
+    const int64_t *flag[4], *pos[4];
+    int32_t *out[4];
+};
+__global__ __launch_bounds__(256) void k_compact(CompactBatch c, int nboxes)
 {
     int b = blockIdx.x * 256 + threadIdx.x;
     if (b >= nboxes) return;
-    if (flag[b]) out[pos[b]] = b;
+    const int w = blockIdx.y;
+    if (c.flag[w][b]) c.out[w][c.pos[w][b]] = b;
 }
 
-void compact(const int64_t *flag, const int64_t *pos, int nboxes, int32_t *out, hipStream_t s)
+void compact4(const int64_t *const *flag, const int64_t *const *pos, int nboxes, int32_t *const *out, hipStream_t s)
 {
-    k_compact<<<ceil_div(nboxes, 256), 256, 0, s>>>(flag, pos, nboxes, out);
+    CompactBatch c{};
+    for (int w = 0; w < 4; ++w) { c.flag[w] = flag[w]; c.pos[w] = pos[w]; c.out[w] = out[w]; }
+    k_compact<<<dim3(ceil_div(nboxes, 256), 4), 256, 0, s>>>(c, nboxes);
 }
 
 __global__ void k_fill_i32(int32_t *p, int64_t n, int32_t v)
