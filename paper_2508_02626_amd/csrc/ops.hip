@@ -728,26 +728,45 @@ __global__ __launch_bounds__(64) void k_far(const PlanView *V, Bases B)
 // target, the M2P of Sec. 3.2), and its gradient, for every box C of the
 // leaf's W list, added to the near-field sums.  It needs only multipoles and
 // the near field, so it runs after the second P2P part on the side stream,
-// next to the downward pass.  One wavefront per leaf.
+// next to the downward pass.
+// One block per leaf, whose wavefronts share the W list: leaves with a W list are
+// few (8 to 40% of an adaptive tree's) and their lists long (24 boxes at the median,
+// over 100 at the end), so that one wavefront per leaf left the chip idle behind
+// the longest.  Eight wavefronts are better still where there are few such leaves
+// (40 us against 53 at 17,389 Plummer points) but cost occupancy where there are
+// many (414 us against 340 at 250,000).
+// A pass takes up to 64 targets; one of at most 32 or 16 targets splits the
+// wavefront into 2 or 4 groups of lanes, each evaluating another box for the same
+// targets.  The sums of groups and wavefronts are added at the end in their order.
+// What bounds it: FP64 issue (an FMA per coefficient and lane, three with the
+// gradient) at about half its rate, the rest the serial chains of the Horner scheme
+// on two or three wavefronts per SIMD.  Two targets per lane (half the LDS reads)
+// or more wavefronts with the rows evaluated in order did not make it faster.
+// One wavefront per leaf -> this: 17,389 Plummer points, p = 8, 165 -> 53 us;
+// 250,000, p = 12, 606 -> 340 us; 4e6, p = 14, 3.07 -> 2.88 ms; 1e6 Gaussian points,
+// p = 10, potentials alone, leaves of up to 128, 809 -> 420 us.
+constexpr int kM2PWaves = 4;
+template <int P> constexpr int kM2PGroups = ncoef(P) <= 288 ? 4 : 2; // (LDS and registers of the boxes)
 template <int P, bool FLD>
-__global__ __launch_bounds__(64) void k_m2p(const PlanView *V, Bases B)
+__global__ __launch_bounds__(64 * kM2PWaves) __attribute__((amdgpu_waves_per_eu(P < 12 ? 3 : 2, 8))) void k_m2p(
+    const PlanView *V, Bases B)
 {
-    constexpr int NC = (P + 1) * (P + 2) * (P + 3) / 6;
-    __shared__ double cm[NC];
+    constexpr int NC = ncoef(P), GM = kM2PGroups<P>, R = (NC + 63) / 64, NW = kM2PWaves;
+    constexpr int LDC = (NC + 1) / 2 * 2;
+    __shared__ double cm[NW][GM][LDC]; // the boxes' coefficients
+    __shared__ double4 sGeo[64];       // centre and width of the W boxes
+    __shared__ double4 sSum[NW - 1][64];
     int k = find_plan(B, blockIdx.x);
     const PlanView &v = V[k];
     const int box = v.leaves[blockIdx.x - B.b[k]];
     const int64_t w0 = v.W_off[box], w1 = v.W_off[box + 1];
     if (w0 == w1) return;
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const OrderTables &t = *v.tab;
     double cen[3], h;
     box_geom(v, box, cen, h);
     const int f = v.first[box], cnt = v.count[box];
-    // the coefficients of the next W box are loaded into registers (a slice
-    // per lane) while the current box is evaluated
-    constexpr int R = (NC + 63) / 64;
-    double wsc[R], nxt[R];
+    double wsc[R];
     int hp[R]; // LDS position of the lane's coefficients (Horner order)
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -755,61 +774,84 @@ __global__ __launch_bounds__(64) void k_m2p(const PlanView *V, Bases B)
         wsc[r] = a < NC ? t.inv_w[(ea & 255) + ((ea >> 8) & 255) + ((ea >> 16) & 255)] : 0.0;
         hp[r] = horner_pos_of<P>(ea);
     }
-    // W entries are read 64 at a time, lane l holding entry wb + l
-    int64_t wb = w0;
-    int wl = 0;
-    auto load_entries = [&]() { wl = wb + lane < w1 ? v.W_src[wb + lane] : 0; };
-    int nlev = 0;
-    uint64_t nmor = 0;
-    auto fetch = [&](int64_t e) { // raw coefficients and cell of entry e
-        if (e - wb >= 64) { wb += 64; load_entries(); }
-        const int src = __builtin_amdgcn_readlane(wl, (int)(e - wb));
-        const double *Ms = v.M + (int64_t)src * v.ldm;
-#pragma unroll
-        for (int r = 0; r < R; ++r) nxt[r] = lane + 64 * r < NC ? Ms[lane + 64 * r] : 0.0;
-        nlev = v.level[src];
-        nmor = v.morton[src];
-    };
     for (int s = 0; s < cnt; s += 64) {
-        int i = f + s + lane;
-        bool act = s + lane < cnt;
-        double x = act ? v.xs[i] : cen[0], y = act ? v.ys[i] : cen[1], z = act ? v.zs[i] : cen[2];
+        const int rem = cnt - s, G = rem > 32 ? 1 : rem > 16 || GM < 4 ? 2 : 4, L = 64 / G;
+        const int grp = lane / L, tl = lane & (L - 1), i = f + s + tl;
+        const bool act = tl < rem;
+        const double x = act ? v.xs[i] : cen[0], y = act ? v.ys[i] : cen[1], z = act ? v.zs[i] : cen[2];
         double phi = 0.0, gx = 0.0, gy = 0.0, gz = 0.0;
-        wb = w0;
-        load_entries();
-        fetch(w0);
-        for (int64_t e = w0; e < w1; ++e) {
-            __syncthreads(); // the previous box's coefficients are consumed
-#pragma unroll
-            for (int r = 0; r < R; ++r)
-                if (lane + 64 * r < NC) cm[hp[r]] = nxt[r] * wsc[r];
-            const int lev = nlev;
-            const uint64_t mor = nmor;
+        // W entries are read 64 at a time, lane l holding entry wb + l
+        for (int64_t wb = w0; wb < w1; wb += 64) {
+            const int ne = w1 - wb < 64 ? (int)(w1 - wb) : 64;
+            const int wl = v.W_src[wb + (lane < ne ? lane : 0)];
+            __syncthreads(); // the previous entries (and sums) are consumed
+            if (wave == 0) {
+                const int lev = v.level[wl];
+                int cc[3];
+                deinterleave(v.morton[wl], lev, cc);
+                const double hs = v.W / (double)(1ll << lev);
+                sGeo[lane] = make_double4(v.lo[0] + ((double)cc[0] + 0.5) * hs, v.lo[1] + ((double)cc[1] + 0.5) * hs,
+                                          v.lo[2] + ((double)cc[2] + 0.5) * hs, hs);
+            }
             __syncthreads();
-            if (e + 1 < w1) fetch(e + 1);
-            double sc[3];
-            int cc[3];
-            deinterleave(mor, lev, cc);
-            const double hs = v.W / (double)(1ll << lev);
+            for (int e = wave * G; e < ne; e += NW * G) {
+                double mc[GM][R];
 #pragma unroll
-            for (int d = 0; d < 3; ++d) sc[d] = v.lo[d] + ((double)cc[d] + 0.5) * hs;
-            double y0 = x - sc[0], y1 = y - sc[1], y2 = z - sc[2];
-            const double s2 = 1.0 / fma(y2, y2, fma(y1, y1, y0 * y0)), sr = sqrt(s2);
-            double f0, fx, fy, fz;
-            eval_poly<P, FLD>(cm, y0 * s2 * hs, y1 * s2 * hs, y2 * s2 * hs, f0, fx, fy, fz);
-            phi = fma(sr, f0, phi);
-            if constexpr (FLD) {
-                const double yf = y0 * fx + y1 * fy + y2 * fz;
-                gx += sr * (-y0 * s2 * f0 + hs * s2 * fx - 2.0 * hs * s2 * s2 * y0 * yf);
-                gy += sr * (-y1 * s2 * f0 + hs * s2 * fy - 2.0 * hs * s2 * s2 * y1 * yf);
-                gz += sr * (-y2 * s2 * f0 + hs * s2 * fz - 2.0 * hs * s2 * s2 * y2 * yf);
+                for (int g = 0; g < GM; ++g) {
+                    if (g >= G || e + g >= ne) continue;
+                    const double *Ms = v.M + (int64_t)__builtin_amdgcn_readlane(wl, e + g) * v.ldm;
+#pragma unroll
+                    for (int r = 0; r < R; ++r) mc[g][r] = lane + 64 * r < NC ? Ms[lane + 64 * r] : 0.0;
+                }
+                wave_sync(); // the previous boxes' coefficients are consumed
+#pragma unroll
+                for (int g = 0; g < GM; ++g) {
+                    if (g >= G || e + g >= ne) continue;
+#pragma unroll
+                    for (int r = 0; r < R; ++r)
+                        if (lane + 64 * r < NC) cm[wave][g][hp[r]] = mc[g][r] * wsc[r];
+                }
+                wave_sync();
+                const bool on = e + grp < ne; // (a group past the list repeats the first's box)
+                const int ge = on ? grp : 0;
+                const double4 sc = sGeo[e + ge];
+                const double hs = sc.w, y0 = x - sc.x, y1 = y - sc.y, y2 = z - sc.z;
+                const double s2 = 1.0 / fma(y2, y2, fma(y1, y1, y0 * y0)), sr = on ? sqrt(s2) : 0.0;
+                double f0, fx, fy, fz;
+                eval_poly<P, FLD>(cm[wave][ge], y0 * s2 * hs, y1 * s2 * hs, y2 * s2 * hs, f0, fx, fy, fz);
+                if (!on) f0 = fx = fy = fz = 0.0;
+                phi = fma(sr, f0, phi);
+                if constexpr (FLD) {
+                    const double yf = y0 * fx + y1 * fy + y2 * fz;
+                    gx += sr * (-y0 * s2 * f0 + hs * s2 * fx - 2.0 * hs * s2 * s2 * y0 * yf);
+                    gy += sr * (-y1 * s2 * f0 + hs * s2 * fy - 2.0 * hs * s2 * s2 * y1 * yf);
+                    gz += sr * (-y2 * s2 * f0 + hs * s2 * fz - 2.0 * hs * s2 * s2 * y2 * yf);
+                }
             }
         }
-        if (act) v.phi_near[i] += phi;
-        if (FLD && act) { // E = -grad phi
-            v.fld_near[3 * (int64_t)i] -= gx;
-            v.fld_near[3 * (int64_t)i + 1] -= gy;
-            v.fld_near[3 * (int64_t)i + 2] -= gz;
+        for (int o = L; o < 64; o <<= 1) {
+            phi += __shfl_xor(phi, o);
+            if constexpr (FLD) {
+                gx += __shfl_xor(gx, o);
+                gy += __shfl_xor(gy, o);
+                gz += __shfl_xor(gz, o);
+            }
+        }
+        if (wave > 0) sSum[wave - 1][lane] = make_double4(phi, gx, gy, gz);
+        __syncthreads();
+        if (wave == 0 && act && grp == 0) {
+#pragma unroll
+            for (int w = 0; w < NW - 1; ++w) {
+                const double4 o = sSum[w][lane];
+                phi += o.x;
+                if constexpr (FLD) { gx += o.y; gy += o.z; gz += o.w; }
+            }
+            v.phi_near[i] += phi;
+            if constexpr (FLD) { // E = -grad phi
+                v.fld_near[3 * (int64_t)i] -= gx;
+                v.fld_near[3 * (int64_t)i + 1] -= gy;
+                v.fld_near[3 * (int64_t)i + 2] -= gz;
+            }
         }
     }
 }
@@ -1166,8 +1208,8 @@ void launch_p2l_transform(const PlanView *V, const Bases &B, hipStream_t s)
 void launch_m2p(int p, int fld, const PlanView *V, const Bases &B, hipStream_t s)
 {
     if (!nblk(B)) return;
-    if (fld) DISPATCH_PF(p, k_m2p, true, <<<nblk(B), 64, 0, s>>>(V, B))
-    else DISPATCH_PF(p, k_m2p, false, <<<nblk(B), 64, 0, s>>>(V, B))
+    if (fld) DISPATCH_PF(p, k_m2p, true, <<<nblk(B), 64 * kM2PWaves, 0, s>>>(V, B))
+    else DISPATCH_PF(p, k_m2p, false, <<<nblk(B), 64 * kM2PWaves, 0, s>>>(V, B))
 }
 void launch_far(int p, int fld, const PlanView *V, const Bases &B, hipStream_t s)
 {
