@@ -602,13 +602,12 @@ int build_plan(fmm_plan_s *P, const double *xyz)
         int bits = 1;
         while ((1LL << bits) < nb) ++bits;
         const bool tmp = sort_lands_in_tmp((int)mw, 0, bits); // sorted from wv2 into src[3]
-        w_pairs(P->off[2], P->src[2], nb, wk, tmp ? wv2 : P->src[3], s);
-        radix_sort_pairs(wk, tmp ? wv2 : P->src[3], wk2, tmp ? P->src[3] : wv2, (int)mw, 0, bits, wscr, s);
         // M2P sources: their full multipoles are rebuilt from the folded ones
         P->wsrc = P->own<int32_t>(nb);
         NOMEM(P->wsrc);
         fill_i32(P->wsrc, nb, 0, s);
-        mark(P->src[2], mw, P->wsrc, s);
+        w_pairs(P->off[2], P->src[2], nb, wk, tmp ? wv2 : P->src[3], P->wsrc, s);
+        radix_sort_pairs(wk, tmp ? wv2 : P->src[3], wk2, tmp ? P->src[3] : wv2, (int)mw, 0, bits, wscr, s);
     }
     int *octoff = P->temp<int>(kOctOffsetInts);
     uint64_t *okey = P->temp<uint64_t>(nt + 1), *otk = P->temp<uint64_t>(nt + 1);

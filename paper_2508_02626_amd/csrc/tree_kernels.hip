@@ -776,21 +776,29 @@ void uwlist(const TreeArgs &a, const int32_t *coll, int which, int64_t *ucnt, co
 }
 
 // X = transpose of W: pairs (key = source box, value = target box), stably
-// sorted by source; targets arrive in ascending order.
+// sorted by source; targets arrive in ascending order.  used[source] is set (the
+// boxes M2P reads).  kPairLanes lanes write a box's list: few boxes have one, of
+// up to 150 entries; a thread per box took 23 us at 17,389 Plummer points and 33 at 100,000
+// Gaussian ones (their plan and evaluation 1085 -> 1048 us with this form).
+constexpr int kPairLanes = 16;
 __global__ __launch_bounds__(256) void k_w_pairs(const int64_t *woff, const int32_t *wsrc, int nboxes,
-                                                 uint64_t *key, int32_t *val)
+                                                 uint64_t *key, int32_t *val, int32_t *used)
 {
-    int b = blockIdx.x * 256 + threadIdx.x;
+    const int b = blockIdx.x * (256 / kPairLanes) + threadIdx.x / kPairLanes;
     if (b >= nboxes) return;
-    for (int64_t e = woff[b]; e < woff[b + 1]; ++e) {
-        key[e] = (uint64_t)wsrc[e];
+    const int64_t e1 = woff[b + 1];
+    for (int64_t e = woff[b] + threadIdx.x % kPairLanes; e < e1; e += kPairLanes) {
+        const int32_t src = wsrc[e];
+        key[e] = (uint64_t)src;
         val[e] = b;
+        used[src] = 1;
     }
 }
 
-void w_pairs(const int64_t *woff, const int32_t *wsrc, int nboxes, uint64_t *key, int32_t *val, hipStream_t s)
+void w_pairs(const int64_t *woff, const int32_t *wsrc, int nboxes, uint64_t *key, int32_t *val, int32_t *used,
+             hipStream_t s)
 {
-    k_w_pairs<<<ceil_div(nboxes, 256), 256, 0, s>>>(woff, wsrc, nboxes, key, val);
+    k_w_pairs<<<ceil_div(nboxes, 256 / kPairLanes), 256, 0, s>>>(woff, wsrc, nboxes, key, val, used);
 }
 
 // ---------------- work lists ----------------
@@ -843,17 +851,6 @@ __global__ void k_fill_i32(int32_t *p, int64_t n, int32_t v)
 void fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s)
 {
     if (n > 0) k_fill_i32<<<ceil_div(n, 256), 256, 0, s>>>(p, n, v);
-}
-
-__global__ void k_mark(const int32_t *idx, int64_t n, int32_t *flag)
-{
-    int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) flag[idx[i]] = 1;
-}
-
-void mark(const int32_t *idx, int64_t n, int32_t *flag, hipStream_t s)
-{
-    if (n > 0) k_mark<<<ceil_div(n, 256), 256, 0, s>>>(idx, n, flag);
 }
 
 } // namespace fmm
