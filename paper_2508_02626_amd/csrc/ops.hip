@@ -11,6 +11,7 @@
 //        in full only to complete the expansions for export.
 //   L2L  (Sec. 2.5) child Lhat += G_octant * parent Lhat, applied to the
 //        harmonic components (GH_octant) before the leaves are unfolded.
+//        (M2M and L2L are here for orders below 6; from 6 on in translate.hip.)
 //   L2P / M2P (Sec. 3.2) share one evaluation routine (nested Horner with the
 //        gradient); M2P evaluates phi = |d| phi_M(d), d = y/|y|^2 (Eq. P2M_phi).
 //   P2L  (Sec. 2.4) Lhat_b += q d^b(1/|x|) at x = (c - x_i)/h, through inverse
