@@ -932,7 +932,9 @@ __device__ inline double rsqrt_or_zero(double x)
 // KIND 0 (FP64) and 1 (FP32 terms): a pair contributes iff r^2 > 0, which
 // skips j == i (same coordinates) and coincident points alike.  KIND 2 (the
 // softened kernel, FP64): every j != i with r^2 + eps^2 > 0.
-// FLD: the field terms too (phi is the same bits either way).
+// FLD: the field terms too (phi is the same bits either way).  The charge goes
+// into the product first: below about 1e-154 apart ri * ri alone overflows,
+// and would make a NaN of a zero charge's term (the padding's among them).
 template <int MIXED, bool FLD>
 __device__ inline void p2p_range(const SrcT<MIXED> *S, int n, Tgt &a, Tgt &b, double eps2)
 {
@@ -943,7 +945,7 @@ __device__ inline void p2p_range(const SrcT<MIXED> *S, int n, Tgt &a, Tgt &b, do
             const double ri = (s.j != t.i && r2 > 0.0) ? rsqrt_refined(r2) : 0.0;
             t.phi = fma(s.q, ri, t.phi);
             if constexpr (FLD) {
-                const double qr3 = s.q * ri * (ri * ri);
+                const double qr3 = s.q * ri * ri * ri;
                 t.ex = fma(qr3, dx, t.ex); t.ey = fma(qr3, dy, t.ey); t.ez = fma(qr3, dz, t.ez);
             }
         };
@@ -981,7 +983,7 @@ __device__ inline void p2p_range(const SrcT<MIXED> *S, int n, Tgt &a, Tgt &b, do
             const double ri = rsqrt_or_zero(r2);
             t.phi = fma(s.q, ri, t.phi);
             if constexpr (FLD) {
-                const double qr3 = s.q * ri * (ri * ri);
+                const double qr3 = s.q * ri * ri * ri;
                 t.ex = fma(qr3, dx, t.ex); t.ey = fma(qr3, dy, t.ey); t.ez = fma(qr3, dz, t.ez);
             }
         };
