@@ -750,16 +750,17 @@ constexpr int kM2PWaves = 4;
 template <int P> constexpr int kM2PGroups = ncoef(P) <= 288 ? 4 : 2; // (LDS and registers of the boxes)
 template <int P, bool FLD>
 __global__ __launch_bounds__(64 * kM2PWaves) __attribute__((amdgpu_waves_per_eu(P < 12 ? 3 : 2, 8))) void k_m2p(
-    const PlanView *V, Bases B)
+    const PlanView *V, Bases B, int block0)
 {
     constexpr int NC = ncoef(P), GM = kM2PGroups<P>, R = (NC + 63) / 64, NW = kM2PWaves;
     constexpr int LDC = (NC + 1) / 2 * 2;
     __shared__ double cm[NW][GM][LDC]; // the boxes' coefficients
     __shared__ double4 sGeo[64];       // centre and width of the W boxes
     __shared__ double4 sSum[NW - 1][64];
-    int k = find_plan(B, blockIdx.x);
+    const int block = block0 + (int)blockIdx.x;
+    int k = find_plan(B, block);
     const PlanView &v = V[k];
-    const int box = v.leaves[blockIdx.x - B.b[k]];
+    const int box = v.leaves[block - B.b[k]];
     const int64_t w0 = v.W_off[box], w1 = v.W_off[box + 1];
     if (w0 == w1) return;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1210,9 +1211,14 @@ void launch_p2l_transform(const PlanView *V, const Bases &B, hipStream_t s)
 }
 void launch_m2p(int p, int fld, const PlanView *V, const Bases &B, hipStream_t s)
 {
-    if (!nblk(B)) return;
-    if (fld) DISPATCH_PF(p, k_m2p, true, <<<nblk(B), 64 * kM2PWaves, 0, s>>>(V, B))
-    else DISPATCH_PF(p, k_m2p, false, <<<nblk(B), 64 * kM2PWaves, 0, s>>>(V, B))
+    // a launch holds fewer than 2^32 threads: at four wavefronts a leaf, larger
+    // plans and batches take several
+    constexpr unsigned kMost = 0xffffffffu / (64 * kM2PWaves);
+    for (unsigned b0 = 0; b0 < nblk(B); b0 += kMost) {
+        const unsigned n = nblk(B) - b0 < kMost ? nblk(B) - b0 : kMost;
+        if (fld) DISPATCH_PF(p, k_m2p, true, <<<n, 64 * kM2PWaves, 0, s>>>(V, B, (int)b0))
+        else DISPATCH_PF(p, k_m2p, false, <<<n, 64 * kM2PWaves, 0, s>>>(V, B, (int)b0))
+    }
 }
 void launch_far(int p, int fld, const PlanView *V, const Bases &B, hipStream_t s)
 {
