@@ -204,7 +204,7 @@ struct fmm_plan_s {
     bool user_alloc = false;
     std::vector<std::pair<void *, size_t>> bufs;  // owned, freed by destroy
     std::vector<std::pair<void *, size_t>> temps; // freed at the end of the build
-    size_t footprint = 0;
+    size_t footprint = 0, estimate = 0; // device bytes held, and fmm_plan_estimate's
     double root[4] = {0, 0, 0, 1};
     int p = 0, nc = 0, nh = 0, ldm = 0, ldh = 0, ldmh = 0, D = 0, depth = 0, leaf_size = 0;
     int uniform = 0, precision = 0, mixed_m2l = 0, m2l_rot = 0;
@@ -373,6 +373,58 @@ struct Sizer {
     template <typename T> Sizer &add(size_t count) { total += fmm_plan_s::rounded(sizeof(T) * count); return *this; }
 };
 
+// M2L slots of a plan: `nt` targets in `groups` groups, each starting a tile
+int64_t m2l_slot_cap(int64_t nt, int groups)
+{
+    const int64_t c = (nt + (int64_t)groups * (kM2LSlots - 1) + kM2LSlots - 1) / kM2LSlots * kM2LSlots;
+    return std::max<int64_t>(c, kM2LSlots);
+}
+
+// Device memory of a plan, before its tree is known: per box and particle, with
+// a quarter on top, for a bound on the boxes that no tree comes near (uniform,
+// Gaussian, Plummer and clustered sets reach 0.65 of it).  The slices of partial
+// sums that small trees' M2L parts keep (m2l_parts_of) are added where the box
+// count is known, in a uniform tree.  For an adaptive tree they count only as far
+// as two thirds of the boxes and their slices need more than the bound without
+// slices: below about 10,000 points at 64 a leaf.  A plan takes no more parts than
+// fit below its estimate (build_plan).
+size_t estimate_bytes(int64_t n, int order, int leaf_size, const fmm_options_t &o)
+{
+    const bool soft = o.kernel == FMM_KERNEL_SOFTENED;
+    double boxes;
+    if (o.uniform_depth >= 0) {
+        boxes = 0;
+        for (int l = 0, s = 1; l <= o.uniform_depth; ++l, s *= 8) boxes += s;
+    } else {
+        boxes = 1 + 8.0 * 2.0 * n / (leaf_size + 1);
+    }
+    double ldm = pad16(ncoef(order)), ldh = pad16(nharm(order)), ldmh = folded_ld(order);
+    const int base = m2l_base_parts(order), parts = m2l_parts_add(order, base) ? 1 : base;
+    double per_box = 8 * (2 * ldm + parts * ldh + ldmh) + 4 * ldmh + 4 * 200 + 64; // expansions, slots, lists
+    double per_particle = 8 * 3 + 4 + 8 * 5 + 8 * 2;
+    double total = boxes * per_box + n * per_particle + 8 * 27 * boxes;
+    double known = 0, small = 0; // slices; a small tree with its slices
+    if (!soft && o.m2l_method != FMM_M2L_ROTATION) {
+        auto slices = [&](double nb, int np) { return 8 * ldh * nb * (np - parts); };
+        if (o.uniform_depth >= 2) { // (V lists at every level from 2 on)
+            const int np = m2l_parts_of(order, m2l_slot_cap((int64_t)boxes - 9, 8) / kM2LSlots, (int64_t)boxes);
+            if (np > base) known = slices(boxes, np);
+        } else if (o.uniform_depth < 0) {
+            for (int np = base + 1; np <= kM2LMaxParts; ++np) { // the largest tree of np parts, at most
+                const int tiles = (kM2LFillBlocks - 1) / (np - 1);
+                const double nb = std::min(std::floor(boxes * 2 / 3), (double)std::min(64 * (tiles - 8) + 8, kM2LSliceRows / (np - 1)));
+                if (nb >= 1) small = std::max(small, nb * (per_box + 8 * 27) + n * per_particle + slices(nb, np));
+            }
+        }
+    }
+    const int depth = o.uniform_depth >= 0 ? o.uniform_depth : o.max_depth;
+    if (soft && depth >= 2 && order <= kSoftMaxOrder)
+        total += 8.0 * (depth - 1) * 343 * soft_table_ldc(order); // derivative tables per level (at most)
+    if (soft && order >= kSoftSymOrder && order <= kSoftSymMaxOrder)
+        total += boxes * 8.0 * (soft_sym_ld(order) - ldmh); // class-ordered moments instead of folded ones
+    return (size_t)std::max(total * 1.25 + known, small);
+}
+
 // Plan construction, stream-ordered on the plan's stream with three host
 // synchronisations (two for a uniform tree): the box count of an adaptive
 // tree, the list and work-list sizes, and the end of the build.
@@ -381,11 +433,13 @@ int build_plan(fmm_plan_s *P, const double *xyz)
     hipStream_t s = P->stream;
     const int n = P->n;
     const bool adaptive = !P->uniform;
+    size_t owned = 0; // bytes of the buffers the plan keeps
     // ---- phase A: particles (sizes known from n)
     {
         Sizer o;
         o.add<int32_t>(n).add<double>(n).add<double>(n).add<double>(n).add<double>(n).add<double>(n).add<double>(3ull * n);
         if (!P->reserve(true, o.total)) return fail(FMM_ENOMEM, "device allocation failed (particles)");
+        owned += o.total;
         Sizer t;
         t.add<double>(4).add<double>(6 * kBBoxBlocks).add<int>(1).add<uint64_t>(n).add<uint64_t>(n).add<int32_t>(n)
          .add<int32_t>(sort_scratch_bytes(n) / 4 + 1);
@@ -457,6 +511,7 @@ int build_plan(fmm_plan_s *P, const double *xyz)
             if (P->mixed_m2l && m2l_f32_operands(P->p)) o.add<float>((size_t)(nb + 1) * P->ldmh);
         }
         if (!P->reserve(true, o.total)) return fail(FMM_ENOMEM, "device allocation failed (boxes)");
+        owned += o.total;
         Sizer t;
         if (adaptive)
             t.add<uint64_t>(nb).add<int32_t>(nb).add<uint64_t>(nb).add<int32_t>(nb).add<int32_t>(nb).add<int32_t>(nb)
@@ -565,18 +620,22 @@ int build_plan(fmm_plan_s *P, const double *xyz)
     // ---- phase C: list contents and M2L tiles (sizes known)
     const int by_level = soft && !P->uniform; // (the softened kernel's tables depend on the level)
     const int tile_groups = 8 * (by_level ? std::max(depth - 1, 1) : 1); // V lists: levels 2..depth
-    int64_t slot_cap = ((int64_t)nt + tile_groups * (kM2LSlots - 1) + kM2LSlots - 1) / kM2LSlots * kM2LSlots;
-    if (slot_cap < kM2LSlots) slot_cap = kM2LSlots;
+    const int64_t slot_cap = m2l_slot_cap(nt, tile_groups);
     const int64_t mw = P->nlist[2];
-    P->m2l_parts = (P->m2l_rot || soft) ? 1 : m2l_parts_of(P->p, slot_cap / kM2LSlots, nb);
+    P->m2l_parts = (P->m2l_rot || soft) ? 1 : m2l_parts_of(P->p, nt ? slot_cap / kM2LSlots : 0, nb);
     // partial sums of the M2L parts after the first
-    const bool lh2 = P->m2l_parts > 1 && !m2l_parts_add(P->p, P->m2l_parts);
+    auto slice_rows = [&] { return m2l_parts_add(P->p, P->m2l_parts) ? 0 : (size_t)(P->m2l_parts - 1) * nb; };
     {
         Sizer o;
-        if (lh2) o.add<double>((size_t)(P->m2l_parts - 1) * nb * P->ldh);
         for (int w = 0; w < 4; ++w)
             if (w != 1) o.add<int32_t>(P->nlist[w] ? P->nlist[w] : 1);
+        if (mw > 0) o.add<int32_t>(nb);
         o.add<int32_t>(slot_cap);
+        // parts beyond the base count as far as the estimate reaches (an adaptive
+        // tree near the bound on its boxes gets fewer)
+        while (P->m2l_parts > m2l_base_parts(P->p) && owned + o.total + 8 * P->ldh * slice_rows() > P->estimate)
+            --P->m2l_parts;
+        if (slice_rows()) o.add<double>(slice_rows() * P->ldh);
         if (!P->reserve(true, o.total)) return fail(FMM_ENOMEM, "device allocation failed (list arrays)");
         Sizer t;
         if (mw > 0) t.add<uint64_t>(mw).add<uint64_t>(mw).add<int32_t>(mw).add<int32_t>(sort_scratch_bytes((int)mw) / 4 + 1);
@@ -591,8 +650,8 @@ int build_plan(fmm_plan_s *P, const double *xyz)
     }
     int32_t *slots = P->own<int32_t>(slot_cap);
     NOMEM(slots);
-    double *Lh2 = lh2 ? P->own<double>((size_t)(P->m2l_parts - 1) * nb * P->ldh) : nullptr;
-    if (lh2) NOMEM(Lh2);
+    double *Lh2 = slice_rows() ? P->own<double>(slice_rows() * P->ldh) : nullptr;
+    if (slice_rows()) NOMEM(Lh2);
     if (P->uniform) ulist_uniform(ta, 1, nullptr, nullptr, nullptr, P->off[0], P->src[0], s);
     else uwlist(ta, coll, 1, nullptr, P->off[0], P->src[0], nullptr, P->off[2], P->src[2], nullptr, s);
     if (mw > 0) { // X = transpose of W
@@ -733,6 +792,7 @@ extern "C" int fmm_plan(const double *xyz_dev, int64_t n, int32_t order, int32_t
         if (!P->rot) { delete P; return fail(FMM_EDEVICE, err); }
     }
     P->n = (int)n;
+    P->estimate = estimate_bytes(n, order, leaf_size, o);
     P->tab = tab;
     if (o.root) for (int k = 0; k < 4; ++k) P->root[k] = o.root[k];
     else P->root[3] = -1.0;
@@ -1298,26 +1358,7 @@ extern "C" int fmm_plan_estimate(int64_t n, int32_t order, int32_t leaf_size, co
     fmm_options_t o;
     fmm_default_options(&o);
     if (opt) o = *opt;
-    double boxes;
-    if (o.uniform_depth >= 0) {
-        boxes = 0;
-        for (int l = 0, s = 1; l <= o.uniform_depth; ++l, s *= 8) boxes += s;
-    } else {
-        boxes = 1 + 8.0 * 2.0 * n / (leaf_size + 1);
-    }
-    double ldm = pad16(ncoef(order)), ldh = pad16(nharm(order)), ldmh = folded_ld(order);
-    const int parts = m2l_parts_add(order, m2l_base_parts(order)) ? 1 : m2l_base_parts(order);
-    double per_box = 8 * (2 * ldm + parts * ldh + ldmh) + 4 * ldmh + 4 * 200 + 64; // expansions, slots, lists
-    // slices of the M2L parts of small trees
-    const double slices = 8 * ldh * std::min((kM2LMaxParts - 1) * boxes, (double)kM2LSliceRows);
-    double per_particle = 8 * 3 + 4 + 8 * 5 + 8 * 2;
-    double total = boxes * per_box + slices + n * per_particle + 8 * 27 * boxes;
-    const int depth = o.uniform_depth >= 0 ? o.uniform_depth : o.max_depth;
-    if (o.kernel == FMM_KERNEL_SOFTENED && depth >= 2 && order <= kSoftMaxOrder)
-        total += 8.0 * (depth - 1) * 343 * soft_table_ldc(order); // derivative tables per level (at most)
-    if (o.kernel == FMM_KERNEL_SOFTENED && order >= kSoftSymOrder && order <= kSoftSymMaxOrder)
-        total += boxes * 8.0 * (soft_sym_ld(order) - ldmh); // class-ordered moments instead of folded ones
-    *bytes = (size_t)(total * 1.25);
+    *bytes = estimate_bytes(n, order, leaf_size, o);
     return FMM_OK;
 }
 
