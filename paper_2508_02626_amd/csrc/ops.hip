@@ -1051,6 +1051,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void
             sPre[lane] = incl - bc;
             sOff[lane] = bf - (incl - bc);
             wave_sync();
+            // (the last batch ends the stream and flushes what is staged: its total is
+            // not zero while there is something, as an adaptive tree has no empty
+            // boxes and a uniform tree's lists are one batch, 27 boxes at most)
             const bool last = ub + 64 >= u1;
             for (int s0 = 0; s0 < total;) {
                 const int take = min(total - s0, CH - m);
