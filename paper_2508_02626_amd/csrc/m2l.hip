@@ -365,22 +365,18 @@ template <int P> struct SymShape {
     static constexpr int RT = sym_row_tiles(P), KS = sym_ksteps(P), RP = sym_row_pairs(P);
     static constexpr int KSV = (KS + 1) / 2, ZOFF = 8 * dlayout_s2(P); // (sym_engine.h)
     int rc[RT], kc[KS]; // parity class of each row tile and k-step
-    int kb[9];          // first k-step of each column class
     uint64_t tau[3][2]; // bit ks of tau[b]: bit b of k-step ks's class
     // pairs of row tiles: tile t of parity class (x, y, 0) and tile t of
     // (x, y, 1), numbered in the order of the z = 0 tiles.  The (i, j, 1) rows of
     // a class, in increasing degree, have the (i, j) of the first (i, j, 0)
     // rows, so the D addresses of a pair differ by the z stride alone
     int pt[RP], pr[RT]; // z = 0 tile of a pair, pair of a row tile
-    constexpr SymShape() : rc(), kc(), kb(), tau(), pt(), pr()
+    constexpr SymShape() : rc(), kc(), tau(), pt(), pr()
     {
         for (int r = 0; r < RT; ++r) rc[r] = sym_tile_class(P, r, true);
         int k = 0;
-        for (int c = 0; c < 8; ++c) {
-            kb[c] = k;
+        for (int c = 0; c < 8; ++c)
             for (int t = 0; t < sym_class_ksteps(P, c); ++t) kc[k++] = c;
-        }
-        kb[8] = k;
         for (int ks = 0; ks < KS; ++ks)
             for (int b = 0; b < 3; ++b) tau[b][ks / 64] |= (uint64_t)((kc[ks] >> b) & 1) << (ks % 64);
         int tn[RT] = {}, q = 0;
@@ -393,6 +389,7 @@ template <int P> struct SymShape {
                 if ((rc[r] | 1) == (rc[pt[i]] | 1) && tn[r] == tn[pt[i]]) pr[r] = i;
     }
 };
+
 // Run by one whole wavefront: from the mask of classes used by a tile's
 // targets, list them in class order (sList), note where each zero mask's
 // classes end in the list (sZend; the table orders classes by zero mask) and
