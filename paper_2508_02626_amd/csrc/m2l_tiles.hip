@@ -22,9 +22,10 @@ namespace fmm {
 // run at the same time hold the children of the same parents, whose V lists
 // draw on the same source boxes.
 // by_level (the softened kernel's adaptive trees, whose tables depend on the
-// level): every (octant, level) group starts a tile of its own, so that no tile
-// runs the classes of two levels one after the other (1e6 Plummer points, 64 a
-// leaf: 51 of 944 tiles did, up to three times as long as the others).
+// level): every (octant, level) group starts a tile of its own, as the softened
+// M2L kernels require (soft_tile_level): they run one level's tables per tile.
+// Tiles across a level boundary ran the classes of both levels one after the other
+// (1e6 Plummer points, 64 a leaf: 51 of 944 tiles, up to three times as long).
 constexpr int kCatBits = 12;
 constexpr int kTileLevels = kMaxDepth + 1;
 

@@ -320,25 +320,19 @@ __device__ inline void soft_tile_targets(const PlanView &v, const SoftGrid &G, i
     }
 }
 
-// Levels of the targets (sLv, -1 for empty places) and, in info, their level
-// range and octant (info[1] < 0: no target).  sTg must be visible to the block.
-__device__ inline void soft_tile_levels(const PlanView &v, int tid, const int *sTg, int *sLv, int *info)
+// Level (-1: no target) and octant of the tile's targets: every tile holds one
+// level, a uniform tree's by its layout above, an adaptive softened plan's because
+// m2l_tiles starts a tile at each (octant, level).  The M2L kernels run that
+// level's tables for all 64: a tile builder that mixes levels needs other kernels.
+// sTg must be visible to the block.
+__device__ inline void soft_tile_level(const PlanView &v, int tid, const int *sTg, int *info)
 {
-    if (tid < 64) { // (one wavefront, a target per lane)
+    if (tid < 64) { // (one wavefront: the first target's)
         const int g = sTg[tid];
-        const int lv = g >= 0 ? v.level[g] : -1, oc = g >= 0 ? (int)(v.morton[g] & 7) : 0;
-        sLv[tid] = lv;
-        int lo = g >= 0 ? lv : 1 << 30, hi = lv;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            lo = min(lo, __shfl_xor(lo, o));
-            hi = max(hi, __shfl_xor(hi, o));
-        }
         const unsigned long long have = __ballot(g >= 0);
         if (tid == (have ? __ffsll(have) - 1 : 0)) {
-            info[0] = lo;
-            info[1] = hi;
-            info[2] = oc;
+            info[0] = have ? v.level[g] : -1;
+            info[1] = have ? (int)(v.morton[g] & 7) : 0;
         }
     }
     __syncthreads();
@@ -353,10 +347,7 @@ __device__ inline void soft_tile_levels(const PlanView &v, int tid, const int *s
 // vector ahead.  Tables are double-buffered in LDS (one barrier per slot).
 // The 64 targets of a block share the 189 offsets of one octant: in a uniform
 // tree 64 boxes of one level and octant (Morton index 8 (64 t + i) + o); in an
-// adaptive tree the plan's M2L target tiles, whose targets are in level order
-// within their octant, so that only the tiles at a level boundary hold two
-// levels.  A block runs its levels one after the other with that level's
-// tables; a target's operands are zero in the other levels' products.
+// adaptive tree the plan's M2L target tiles, each of one octant and level.
 template <int P> struct SoftM2L {
     static constexpr int NP = ncoef(P), MT = (NP + 15) / 16, KS = ((NP + 3) / 4 + 1) & ~1, KSV = KS / 2;
     static constexpr int LDD = SoftCube<P>::LDD, LDC = (ncoef(2 * P) + 1) & ~1;
@@ -372,9 +363,9 @@ __global__ __launch_bounds__(256) void k_m2l_soft(const PlanView *V, SoftGrid G)
     typedef double vec_t __attribute__((ext_vector_type(2)));
     __shared__ double sD[2][LDD];
     __shared__ int sHo[4][KS];
-    __shared__ int sTg[64], sLv[64];
+    __shared__ int sTg[64];
     __shared__ int sList[kVSlots];
-    __shared__ int sN, sInfo[3];
+    __shared__ int sN, sInfo[2];
     const PlanView &v = V[0];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, col = lane & 15, kq = lane >> 4;
     const OrderTables &tb = *v.tab;
@@ -390,12 +381,12 @@ __global__ __launch_bounds__(256) void k_m2l_soft(const PlanView *V, SoftGrid G)
         hb[mt] = b < NP ? SoftCube<P>::addr(gptr(tb.exps)[b]) : 0;
     }
     __syncthreads();
-    soft_tile_levels(v, tid, sTg, sLv, sInfo);
-    const int lmin = sInfo[0], lmax = sInfo[1], oct = sInfo[2];
-    if (lmax < 0) return; // (block-uniform)
+    soft_tile_level(v, tid, sTg, sInfo);
+    const int lev = sInfo[0], oct = sInfo[1];
+    if (lev < 0) return; // (block-uniform)
     const auto vs = gptr(v.vslot);
     const auto offs = gptr(tb.offs) + oct * kVSlots;
-    const int tgt = sTg[wave * 16 + col], tlev = sLv[wave * 16 + col];
+    const int tgt = sTg[wave * 16 + col];
     typedef double dvec_t __attribute__((ext_vector_type(2)));
     dvec_t pd[DV];
     int dm[DV][2];
@@ -410,81 +401,79 @@ __global__ __launch_bounds__(256) void k_m2l_soft(const PlanView *V, SoftGrid G)
     double4_t acc[MT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) acc[mt] = double4_t{0, 0, 0, 0};
-    for (int L = lmin; L <= lmax; ++L) {
-        // slots used by the block's targets of level L, in increasing order
-        if (tid < kVSlots) {
-            int any = 0;
-            for (int q = 0; q < 64; ++q) any |= sLv[q] == L && vs[(int64_t)sTg[q] * kVSlots + tid] >= 0;
-            sList[tid] = any;
+    // slots used by the block's targets, in increasing order
+    if (tid < kVSlots) {
+        int any = 0;
+        for (int q = 0; q < 64; ++q) any |= sTg[q] >= 0 && vs[(int64_t)sTg[q] * kVSlots + tid] >= 0;
+        sList[tid] = any;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        int n = 0;
+        for (int j = 0; j < kVSlots; ++j)
+            if (sList[j]) sList[n++] = j;
+        sN = n;
+    }
+    __syncthreads();
+    const int nslot = sN;
+    const double *Dl = v.Dsoft + (int64_t)(lev - 2) * 343 * LDC;
+    auto load_d = [&](int j) {
+        const dvec_t *Dk = (const dvec_t *)(Dl + (int64_t)offs[j] * LDC);
+#pragma unroll
+        for (int r = 0; r < DV; ++r) {
+            const int e = tid + 256 * r;
+            pd[r] = e < LDC / 2 ? gload(Dk + e) : dvec_t{0, 0};
         }
+    };
+    auto store_d = [&](int buf) {
+#pragma unroll
+        for (int r = 0; r < DV; ++r)
+            if (tid + 256 * r < LDC / 2)
+#pragma unroll
+                for (int w = 0; w < 2; ++w) sD[buf][dm[r][w]] = pd[r][w];
+    };
+    auto row_of = [&](int j) -> const double * {
+        const int src = tgt >= 0 ? vs[(int64_t)tgt * kVSlots + j] : -1;
+        return (src >= 0 ? v.M + (int64_t)src * ldm : v.zrow) + 2 * kq;
+    };
+    const double *rc = v.zrow, *rn = v.zrow;
+    vec_t cur{0, 0}, nxt{0, 0};
+    if (nslot > 0) {
+        load_d(sList[0]);
+        store_d(0);
+        rc = row_of(sList[0]);
+        cur = gload((const vec_t *)rc);
         __syncthreads();
-        if (tid == 0) {
-            int n = 0;
-            for (int j = 0; j < kVSlots; ++j)
-                if (sList[j]) sList[n++] = j;
-            sN = n;
+    }
+    for (int q = 0; q < nslot; ++q) {
+        const int buf = q & 1;
+        const bool more = q + 1 < nslot;
+        if (more) {
+            load_d(sList[q + 1]);
+            rn = row_of(sList[q + 1]);
         }
-        __syncthreads();
-        const int nslot = sN;
-        const double *Dl = v.Dsoft + (int64_t)(L - 2) * 343 * LDC;
-        auto load_d = [&](int j) {
-            const dvec_t *Dk = (const dvec_t *)(Dl + (int64_t)offs[j] * LDC);
-#pragma unroll
-            for (int r = 0; r < DV; ++r) {
-                const int e = tid + 256 * r;
-                pd[r] = e < LDC / 2 ? gload(Dk + e) : dvec_t{0, 0};
-            }
-        };
-        auto store_d = [&](int buf) {
-#pragma unroll
-            for (int r = 0; r < DV; ++r)
-                if (tid + 256 * r < LDC / 2)
-#pragma unroll
-                    for (int w = 0; w < 2; ++w) sD[buf][dm[r][w]] = pd[r][w];
-        };
-        auto row_of = [&](int j) -> const double * {
-            const int src = tgt >= 0 && tlev == L ? vs[(int64_t)tgt * kVSlots + j] : -1;
-            return (src >= 0 ? v.M + (int64_t)src * ldm : v.zrow) + 2 * kq;
-        };
-        const double *rc = v.zrow, *rn = v.zrow;
-        vec_t cur{0, 0}, nxt{0, 0};
-        if (nslot > 0) {
-            load_d(sList[0]);
-            store_d(0);
-            rc = row_of(sList[0]);
-            cur = gload((const vec_t *)rc);
-            __syncthreads();
-        }
-        for (int q = 0; q < nslot; ++q) {
-            const int buf = q & 1;
-            const bool more = q + 1 < nslot;
-            if (more) {
-                load_d(sList[q + 1]);
-                rn = row_of(sList[q + 1]);
-            }
-            // the wavefront skips a slot none of its targets has
-            const bool has = rc != v.zrow + 2 * kq;
-            if (__ballot(has)) {
-                const double *D = sD[buf];
+        // the wavefront skips a slot none of its targets has
+        const bool has = rc != v.zrow + 2 * kq;
+        if (__ballot(has)) {
+            const double *D = sD[buf];
 #pragma unroll 1
-                for (int jv = 0; jv < KSV; ++jv) {
-                    nxt = jv + 1 < KSV ? gload((const vec_t *)(rc + 8 * (jv + 1))) : gload((const vec_t *)rn);
+            for (int jv = 0; jv < KSV; ++jv) {
+                nxt = jv + 1 < KSV ? gload((const vec_t *)(rc + 8 * (jv + 1))) : gload((const vec_t *)rn);
 #pragma unroll
-                    for (int w = 0; w < 2; ++w) {
-                        const int ha = sHo[kq][2 * jv + w];
+                for (int w = 0; w < 2; ++w) {
+                    const int ha = sHo[kq][2 * jv + w];
 #pragma unroll
-                        for (int mt = 0; mt < MT; ++mt)
-                            acc[mt] = __builtin_amdgcn_mfma_f64_16x16x4f64(D[hb[mt] + ha], cur[w], acc[mt], 0, 0, 0);
-                    }
-                    cur = nxt;
+                    for (int mt = 0; mt < MT; ++mt)
+                        acc[mt] = __builtin_amdgcn_mfma_f64_16x16x4f64(D[hb[mt] + ha], cur[w], acc[mt], 0, 0, 0);
                 }
-            } else {
-                cur = gload((const vec_t *)rn);
+                cur = nxt;
             }
-            rc = rn;
-            if (more) store_d(buf ^ 1);
-            __syncthreads();
+        } else {
+            cur = gload((const vec_t *)rn);
         }
+        rc = rn;
+        if (more) store_d(buf ^ 1);
+        __syncthreads();
     }
     if (tgt < 0) return;
     double *L = v.L + (int64_t)tgt * ldm;
@@ -650,14 +639,14 @@ __global__ __launch_bounds__(256, 1) void k_m2l_soft_sym(const PlanView *V, Soft
     typedef double dvec_t __attribute__((ext_vector_type(2)));
     __shared__ double sD[2][LDD];
     __shared__ int sHo[4][KS + 4]; // D byte offset of column (ks, kq); entries past KS are read, not used
-    __shared__ int sTg[64], sLv[64];
+    __shared__ int sTg[64];
     __shared__ int sRep[kSymClasses];
     __shared__ unsigned char sMem[kSymClasses][8]; // member slots (255: none)
     __shared__ unsigned char sSl[kVSlots];         // class of each V slot
     __shared__ unsigned char sList[kSymClasses];
     __shared__ int sZend[8];
     __shared__ unsigned long long sUsed;
-    __shared__ int sN, sInfo[3];
+    __shared__ int sN, sInfo[2];
     int(*sPos)[CMAX] = (int(*)[CMAX]) & sD[1][0]; // (set-up and output only)
     const PlanView &v = V[0];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, col = lane & 15, kq = lane >> 4;
@@ -670,9 +659,9 @@ __global__ __launch_bounds__(256, 1) void k_m2l_soft_sym(const PlanView *V, Soft
     soft_tile_targets(v, G, item >> 1, tid, sTg);
     soft_class_positions<P, CMAX>(exps, tid, sPos);
     __syncthreads();
-    soft_tile_levels(v, tid, sTg, sLv, sInfo);
-    const int L = sInfo[1], oct = sInfo[2]; // (every tile holds targets of one level)
-    if (L < 0) return; // (block-uniform)
+    soft_tile_level(v, tid, sTg, sInfo);
+    const int lev = sInfo[0], oct = sInfo[1];
+    if (lev < 0) return; // (block-uniform)
     {
         const auto rep = gptr(tb.srep) + oct * kSymClasses, mem = gptr(tb.smem) + oct * kSymClasses * 8;
         const auto ssl = gptr(tb.sslot) + oct * kVSlots;
@@ -747,7 +736,7 @@ __global__ __launch_bounds__(256, 1) void k_m2l_soft_sym(const PlanView *V, Soft
     __syncthreads();
     const int nq = sN;
     if (nq == 0) return; // (block-uniform)
-    const double *Dl = v.Dsoft + (int64_t)(L - 2) * 343 * LDC;
+    const double *Dl = v.Dsoft + (int64_t)(lev - 2) * 343 * LDC;
     auto load_d = [&](int c) {
         const dvec_t *Dk = (const dvec_t *)(Dl + (int64_t)(sRep[c] & 0xffff) * LDC);
 #pragma unroll
