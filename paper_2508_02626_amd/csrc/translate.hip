@@ -71,9 +71,8 @@ __device__ inline void children_by_axes(const PlanView &v, int parent, int (&ch)
 // A wavefront takes 16 parents of a level: the children's folded vectors are
 // the members of a sign class, their transform the B operands, the matrix
 // streamed from L2 (each operand refilled for the next k-step after its MFMA).
-// Levels whose 16-parent groups do not reach kFillWaves wavefronts give every row
-// tile a wavefront of its own (m2m_tile_waves): it needs one output of the
-// transform per k-step, a signed sum.
+// Levels of few 16-parent groups give every row tile a wavefront of its own
+// (m2m_tile_waves): it needs one output of the transform per k-step, a signed sum.
 template <int P>
 __global__ __launch_bounds__(256) void k_m2m_sym(const PlanView *V, Bases B, int level)
 {
