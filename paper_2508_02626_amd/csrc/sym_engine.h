@@ -71,6 +71,21 @@ template <class SH, int Z> struct SymGroups {
     }
 };
 
+// Walsh-Hadamard transform of o over the axes not in Z, with signs s (+-1) of the
+// axes folded in: output r is that of r ^ (the axes whose sign is -1)
+template <int Z> __device__ __forceinline__ void signed_butterflies(double (&o)[8], const double (&s)[3])
+{
+#pragma unroll
+    for (int st = 0; st < 3; ++st)
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (!((1 << st) & Z) && !(i & (1 << st)) && !(i & Z)) {
+                const double u = o[i], x = o[i | (1 << st)];
+                o[i] = fma(s[st], x, u);
+                o[i | (1 << st)] = fma(-s[st], x, u);
+            }
+}
+
 // One class with zero axes Z.  D + dbase: its table in LDS; Ho: byte offsets of
 // the lane's columns (KS + 4 entries readable); hb: of the lane's rows, per pair;
 // raw[m]: member m's operand vector 0 (in flight; members negating a zero axis
@@ -106,15 +121,7 @@ __device__ __forceinline__ void sym_run_class(const char *D, uint32_t dbase, con
         constexpr int w = decltype(wc)::value;
 #pragma unroll
         for (int m = 0; m < 8; ++m) o[m] = (m & Z) ? 0.0 : raw[m][w];
-#pragma unroll
-        for (int st = 0; st < 3; ++st)
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-                if (!((1 << st) & Z) && !(i & (1 << st)) && !(i & Z)) {
-                    const double u = o[i], x = o[i | (1 << st)];
-                    o[i] = fma(s[st], x, u);
-                    o[i | (1 << st)] = fma(-s[st], x, u);
-                }
+        signed_butterflies<Z>(o, s);
     };
     // the MFMAs of one k-step (its transform hw, group value GC), back to back
     // (sched_barrier keeps what is between them there): each is followed by the

@@ -129,15 +129,7 @@ __global__ __launch_bounds__(256) void k_m2m_sym(const PlanView *V, Bases B, int
             for (int w = 0; w < 2; ++w) {
 #pragma unroll
                 for (int m = 0; m < 8; ++m) h[w][m] = raw[m][w];
-#pragma unroll
-                for (int st = 0; st < 3; ++st)
-#pragma unroll
-                    for (int i = 0; i < 8; ++i)
-                        if (!(i & (1 << st))) {
-                            const double u = h[w][i], x = h[w][i | (1 << st)];
-                            h[w][i] = fma(sg[w][st], x, u);
-                            h[w][i | (1 << st)] = fma(-sg[w][st], x, u);
-                        }
+                signed_butterflies<0>(h[w], sg[w]);
             }
             __builtin_amdgcn_sched_barrier(0);
             const int jn = min(j + 1, KSV - 1);
