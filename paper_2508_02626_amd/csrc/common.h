@@ -138,10 +138,11 @@ __host__ __device__ constexpr bool m2l_sym(int p) { return p >= 6; }
 // classes (or, below order 6, slots) one after the other, about 4 us each: they
 // split a tile into as many parts as bring the launch to about kM2LFillBlocks
 // blocks, one per CU.  2000 points, p = 6, depth 3 (16 tiles): M2L 205 us with
-// two parts, 53 with 16 (a
-// target of 512 blocks: the same at 1e3 to 1e5 points, slower batches).
+// two parts, 53 with 16 (a target of 512 blocks: the same at 1e3 to 1e5 points,
+// slower batches).
 // (The slices of partial sums are bounded to kM2LSliceRows rows, whatever
-// the share of boxes with a V list.)
+// the share of boxes with a V list, and to what the plan's admission estimate
+// leaves them.)
 constexpr int kM2LFillBlocks = 256, kM2LMaxParts = 16, kM2LSliceRows = 2 * 64 * kM2LFillBlocks;
 __host__ __device__ constexpr int m2l_base_parts(int p) { return m2l_sym(p) ? 2 : 1; }
 __host__ __device__ constexpr int m2l_parts_of(int p, int64_t tiles, int64_t nboxes)

@@ -639,7 +639,7 @@ __device__ inline int horner_pos_of(int packed)
 //
 // Potential-only evaluations (FLD = false, here and in k_far, k_m2p, k_p2p and
 // the softened M2P): the gradient is three quarters of the FMAs per
-// coefficient and, in P2P, 7 of about 25 issue slots per pair, and was computed
+// coefficient and, in P2P, 6 of 21 vector instructions per pair, and was computed
 // and stored also when the caller passes no field array.  A launch leaves it
 // out when none of its plans has one (1e6 Gaussian points, p = 10, leaves of
 // up to 128, potentials only: 5.26 -> 4.55 ms per evaluation).
@@ -871,9 +871,9 @@ __global__ __launch_bounds__(64 * kM2PWaves) __attribute__((amdgpu_waves_per_eu(
 // position in the stream of their particles into a particle, so that a chunk of
 // kP2PChunk sources, whatever boxes it spans, is one set of loads per lane, staged
 // in LDS as 32-byte records.
-// What bounds it: FP64 issue, 21 instructions and a reciprocal square root per
-// pair and lane (0.57 ms for the 8.2e8 pairs of 1e6 uniform points at depth 5 with
-// every lane busy).  Filling chunks box by box, with the ranges' lengths divided
+// What bounds it: FP64 issue, 21 vector instructions per pair and lane, a
+// reciprocal square root among them (0.57 ms for the 8.2e8 pairs of 1e6 uniform
+// points at depth 5 with every lane busy; 15 instructions without the field).  Filling chunks box by box, with the ranges' lengths divided
 // out per chunk and lanes of unequal ranges masked off, took 0.91 ms there and
 // 3.9 ms on 4e6 Plummer points; this form takes 0.81 and 3.3 (with chunks of 64: 0.84
 // and 3.4).
