@@ -919,17 +919,17 @@ int nonleaf_groups(const fmm_plan_s *P, int level)
     return (int)ceil_div(c, 16);
 }
 // blocks of the folded M2M and the harmonic L2L at a level (16-parent groups x
-// row tiles per block, or at sign-class orders four wavefronts per block)
+// row tiles per block, or at sign-class orders a wavefront per block)
 int m2m_blocks(const fmm_plan_s *P, int level)
 {
     const int g = nonleaf_groups(P, level);
-    if (m2l_sym(P->p)) return (int)ceil_div((int64_t)g * m2m_tile_waves(sym_row_tiles(P->p), g), 4);
+    if (m2l_sym(P->p)) return g * m2m_tile_waves(sym_row_tiles(P->p), g);
     return g * m2m_row_split(P->ldmh / 16, g);
 }
 int l2l_blocks(const fmm_plan_s *P, int level)
 {
     const int g = nonleaf_groups(P, level);
-    if (m2l_sym(P->p)) return (int)ceil_div((int64_t)g * l2l_tile_waves(sym_row_tiles(P->p), g), 4);
+    if (m2l_sym(P->p)) return g * l2l_tile_waves(sym_row_tiles(P->p), g);
     return g * (P->ldh / 16);
 }
 void m2m(int p, const PlanView *V, const Bases &B, int level, hipStream_t s)

@@ -21,20 +21,20 @@ __host__ __device__ inline int m2m_row_split(int mt, int groups)
     while (2 * r <= mt && mt % (2 * r) == 0 && groups * r < 512) r *= 2;
     return r;
 }
-// Sign-class orders (translate.hip), 4 wavefronts per block.  M2M: wavefronts per
+// Sign-class orders (translate.hip), a wavefront per block.  M2M: wavefronts per
 // 16-parent group: one per row tile where the level's groups would leave SIMDs
 // idle, else one for all mt tiles (each reads all the children).  A launch with one
-// per tile | one for all: order 8, 32 groups 20 | 33 us, 256 groups 40 | 22-34;
-// order 12, 42 groups 38 | 64; order 14, 64 groups 75 | 88, 141 groups 109 | 91,
-// 714 groups 430 | 97.
+// per tile | one for all: order 8, 32 groups 10 | 21 us, 104 groups 16 | 20, 256 groups
+// 42 | 26; order 12, 42 groups 23 | 43; order 14, 64 groups 50 | 56, 141 groups 94 | 56,
+// 714 groups 378 | 80.
 void launch_m2m_sym(int p, const PlanView *V, const Bases &B, int level, hipStream_t s);
 void launch_l2l_sym(int p, const PlanView *V, const Bases &B, int level, hipStream_t s);
 __host__ __device__ inline int m2m_tile_waves(int mt, int groups) { return groups <= 64 ? mt : 1; }
 // L2L: the row tiles of a group spread over up to mt wavefronts until the level
 // has about 2048 (two per SIMD).  A launch with one wavefront per group | until
-// 1024 | 2048 | 4096 | one per tile: order 8, 256 groups 89 | 38 | 53 | 51 | 51 us;
-// order 12, 36 groups 235 | 36 | 36 | 36 | 36; order 14, 714 groups, beside P2P and M2P,
-// 608 | 618 | 563 | 490 | 513, the whole call 38.0 | 38.8 | 37.2 | 37.4 | 37.5 ms.
+// 1024 | 2048 | 4096 | one per tile: order 8, 104 groups 25 | 17 | 21 | 20 | 21 us, 256 groups
+// 43 | 52 | 57 | 57 | 57; order 12, 36 groups 85 | 27 | 27 | 26 | 27; order 14, all levels,
+// beside P2P and M2P, 3.65 | 3.92 | 3.81 | 4.07 | 3.82 ms.
 __host__ __device__ inline int l2l_tile_waves(int mt, int groups)
 {
     const int n = groups > 0 ? 2048 / groups : 1;
