@@ -46,7 +46,7 @@ constexpr int kMaxUniformDepth = 8;
 // arrays, gathered on the device and fetched with one copy.
 struct PlanSizes {
     int64_t tot[4];                  // U, V, W, X list lengths
-    int64_t nleaves, nnonleaf, nxtgt, nmtg;
+    int64_t nleaves, nnonleaf, nxtgt, nmtg, nwtgt;
     int64_t lnl[kMaxDepth + 2];      // non-leaf boxes before each level
     int32_t lvl_begin[kMaxDepth + 2];
     double root[4];
@@ -55,7 +55,7 @@ struct PlanSizes {
 
 __global__ void k_collect_sizes(const int64_t *uoff, const int64_t *voff, const int64_t *woff,
                                 const int64_t *xoff, const int64_t *pleaf, const int64_t *pnon,
-                                const int64_t *px, const int64_t *pv, const int32_t *lvl_begin,
+                                const int64_t *px, const int64_t *pv, const int64_t *pw, const int32_t *lvl_begin,
                                 const double *root, const int *bad, int nb, PlanSizes *out,
                                 int32_t *lnl_off)
 {
@@ -63,6 +63,7 @@ __global__ void k_collect_sizes(const int64_t *uoff, const int64_t *voff, const 
     if (t == 0) {
         out->tot[0] = uoff[nb]; out->tot[1] = voff[nb]; out->tot[2] = woff[nb]; out->tot[3] = xoff[nb];
         out->nleaves = pleaf[nb]; out->nnonleaf = pnon[nb]; out->nxtgt = px[nb]; out->nmtg = pv[nb];
+        out->nwtgt = pw[nb];
         out->bad = *bad;
     }
     if (t < 4) out->root[t] = root[t];
@@ -211,7 +212,7 @@ struct fmm_plan_s {
     const RotTables *rot = nullptr; // rotation-based M2L factors (device)
     int kernel = FMM_KERNEL_COULOMB;  // softened kernel: full expansions, tables per level
     double eps = 0.0;
-    int n = 0, nboxes = 0, nleaves = 0, nxtgt = 0, nslots = 0, m2l_parts = 1;
+    int n = 0, nboxes = 0, nleaves = 0, nxtgt = 0, nwtgt = 0, nslots = 0, m2l_parts = 1;
     int64_t nlist[4] = {0, 0, 0, 0};
     std::vector<int> lvl_begin;       // boxes per level (host)
     std::vector<int> lvl_nonleaf_off; // non-leaf boxes per level (host)
@@ -501,7 +502,7 @@ int build_plan(fmm_plan_s *P, const double *xyz)
          .add<uint64_t>(nb).add<int32_t>(kMaxDepth + 2);
         for (int w = 0; w < 4; ++w) o.add<int64_t>(nb + 1);
         o.add<int32_t>((size_t)nb * kVSlots).add<int32_t>(nb).add<int32_t>(nb).add<int32_t>(nb)
-         .add<int32_t>(kMaxDepth + 2).add<PlanView>(1)
+         .add<int32_t>(nb).add<int32_t>(kMaxDepth + 2).add<PlanView>(1)
          .add<double>((size_t)nb * P->ldm).add<double>((size_t)nb * P->ldm);
         if (soft) {
             o.add<int>(soft_table_ldc(P->p)).add<double>(P->ldm);
@@ -517,9 +518,9 @@ int build_plan(fmm_plan_s *P, const double *xyz)
             t.add<uint64_t>(nb).add<int32_t>(nb).add<uint64_t>(nb).add<int32_t>(nb).add<int32_t>(nb).add<int32_t>(nb)
              .add<uint64_t>(nb).add<int32_t>(sort_scratch_bytes(nb) / 4 + 1);
         t.add<int32_t>(27ull * nb).add<int32_t>(nb);
-        for (int w = 0; w < 8; ++w) t.add<int64_t>(nb + 1);
-        for (int w = 0; w < 4; ++w) t.add<int64_t>(nb + 1);
-        t.add<int64_t>(scan_multi_scratch_bytes(nb, 8) / 8 + 1).add<int32_t>(nb).add<PlanSizes>(1);
+        static_assert(4 + kWorkLists <= kMaxScanBatch, "the lists' and work lists' scans in one set of launches");
+        for (int w = 0; w < 4 + 2 * kWorkLists; ++w) t.add<int64_t>(nb + 1);
+        t.add<int64_t>(scan_multi_scratch_bytes(nb, 4 + kWorkLists) / 8 + 1).add<int32_t>(nb).add<PlanSizes>(1);
         if (!P->reserve(false, t.total)) return fail(FMM_ENOMEM, "device allocation failed (lists)");
     }
     BoxArrays bx{};
@@ -532,7 +533,7 @@ int build_plan(fmm_plan_s *P, const double *xyz)
     P->bx = bx;
     for (int w = 0; w < 4; ++w) { P->off[w] = P->own<int64_t>(nb + 1); NOMEM(P->off[w]); }
     int32_t *vslot = P->own<int32_t>((size_t)nb * kVSlots);
-    int32_t *leaves = P->own<int32_t>(nb), *nonleaf = P->own<int32_t>(nb), *xtgt = P->own<int32_t>(nb);
+    int32_t *leaves = P->own<int32_t>(nb), *nonleaf = P->own<int32_t>(nb), *xtgt = P->own<int32_t>(nb), *wtgt = P->own<int32_t>(nb);
     int32_t *lnl_off = P->own<int32_t>(kMaxDepth + 2);
     P->view_dev = P->own<PlanView>(1);
     double *M = P->own<double>((size_t)nb * P->ldm), *L = P->own<double>((size_t)nb * P->ldm);
@@ -554,7 +555,7 @@ int build_plan(fmm_plan_s *P, const double *xyz)
     } else {
         NOMEM(Mh); NOMEM(Lh);
     }
-    NOMEM(vslot); NOMEM(leaves); NOMEM(nonleaf); NOMEM(xtgt); NOMEM(lnl_off); NOMEM(P->view_dev);
+    NOMEM(vslot); NOMEM(leaves); NOMEM(nonleaf); NOMEM(xtgt); NOMEM(wtgt); NOMEM(lnl_off); NOMEM(P->view_dev);
     NOMEM(M); NOMEM(L);
     if (P->mixed_m2l && m2l_f32_operands(P->p)) NOMEM(Mhf);
     if (adaptive) {
@@ -571,10 +572,10 @@ int build_plan(fmm_plan_s *P, const double *xyz)
     int32_t *leafcol = P->uniform ? nullptr : P->temp<int32_t>(nb);
     TreeArgs ta{bx, lvl_dev, P->D, nb, P->uniform, leafcol};
     int32_t *coll = P->temp<int32_t>(27ull * nb);
-    int64_t *cnt[4], *flg[4], *pos[4];
+    int64_t *cnt[4], *flg[kWorkLists], *pos[kWorkLists];
     for (int w = 0; w < 4; ++w) { cnt[w] = P->temp<int64_t>(nb + 1); NOMEM(cnt[w]); }
-    for (int w = 0; w < 4; ++w) { flg[w] = P->temp<int64_t>(nb + 1); pos[w] = P->temp<int64_t>(nb + 1); NOMEM(flg[w]); NOMEM(pos[w]); }
-    int64_t *mscr = P->temp<int64_t>(scan_multi_scratch_bytes(nb, 8) / 8 + 1);
+    for (int w = 0; w < kWorkLists; ++w) { flg[w] = P->temp<int64_t>(nb + 1); pos[w] = P->temp<int64_t>(nb + 1); NOMEM(flg[w]); NOMEM(pos[w]); }
+    int64_t *mscr = P->temp<int64_t>(scan_multi_scratch_bytes(nb, 4 + kWorkLists) / 8 + 1);
     int32_t *mtg = P->temp<int32_t>(nb);
     PlanSizes *sizes_dev = P->temp<PlanSizes>(1);
     NOMEM(coll); NOMEM(mscr); NOMEM(mtg); NOMEM(sizes_dev);
@@ -588,18 +589,20 @@ int build_plan(fmm_plan_s *P, const double *xyz)
         vlist(ta, coll, 0, cnt[1], nullptr, nullptr, vslot, s); // V counts and M2L slot rows
         uwlist(ta, coll, 0, cnt[0], nullptr, nullptr, cnt[2], nullptr, nullptr, cnt[3], s);
     }
-    flags(bx, nb, cnt[3], cnt[1], flg[0], flg[1], flg[2], flg[3], s);
+    flags(bx, nb, cnt[3], cnt[1], cnt[2], flg, s);
     {
-        const int64_t *in[8] = {cnt[0], cnt[1], cnt[2], cnt[3], flg[0], flg[1], flg[2], flg[3]};
-        int64_t *out[8] = {P->off[0], P->off[1], P->off[2], P->off[3], pos[0], pos[1], pos[2], pos[3]};
-        scan_exclusive_multi(in, out, 8, nb, mscr, s);
+        const int64_t *in[4 + kWorkLists];
+        int64_t *out[4 + kWorkLists];
+        for (int w = 0; w < 4; ++w) { in[w] = cnt[w]; out[w] = P->off[w]; }
+        for (int w = 0; w < kWorkLists; ++w) { in[4 + w] = flg[w]; out[4 + w] = pos[w]; }
+        scan_exclusive_multi(in, out, 4 + kWorkLists, nb, mscr, s);
     }
     {
-        int32_t *out[4] = {leaves, nonleaf, xtgt, mtg};
-        compact4(flg, pos, nb, out, s);
+        int32_t *out[kWorkLists] = {leaves, nonleaf, xtgt, mtg, wtgt};
+        compact(flg, pos, nb, out, s);
     }
     k_collect_sizes<<<1, 64, 0, s>>>(P->off[0], P->off[1], P->off[2], P->off[3], pos[0], pos[1], pos[2], pos[3],
-                                     lvl_dev, root_dev, bad, nb, sizes_dev, lnl_off);
+                                     pos[4], lvl_dev, root_dev, bad, nb, sizes_dev, lnl_off);
     HIPCHK(hipGetLastError());
     if (copy_to_host(&P->sizes, sizes_dev, 1, s)) return FMM_EDEVICE;
     HIPCHK(hipStreamSynchronize(s));
@@ -616,6 +619,7 @@ int build_plan(fmm_plan_s *P, const double *xyz)
     if (Z.tot[2] != Z.tot[3]) return fail(FMM_EDEVICE, "X list size mismatch");
     P->nleaves = (int)Z.nleaves;
     P->nxtgt = (int)Z.nxtgt;
+    P->nwtgt = (int)Z.nwtgt;
     const int nt = (int)Z.nmtg;
     // ---- phase C: list contents and M2L tiles (sizes known)
     const int by_level = soft && !P->uniform; // (the softened kernel's tables depend on the level)
@@ -679,7 +683,7 @@ int build_plan(fmm_plan_s *P, const double *xyz)
     PlanView &v = P->view;
     v.p = P->p; v.nc = P->nc; v.nh = P->nh; v.ldm = P->ldm; v.ldh = P->ldh; v.ldmh = P->ldmh;
     v.precision = P->precision; v.mixed_m2l = P->mixed_m2l; v.depth = P->depth; v.D = P->D;
-    v.n = n; v.nboxes = nb; v.nleaves = P->nleaves; v.nxtgt = P->nxtgt; v.nslots = P->nslots;
+    v.n = n; v.nboxes = nb; v.nleaves = P->nleaves; v.nxtgt = P->nxtgt; v.nwtgt = P->nwtgt; v.nslots = P->nslots;
     for (int k = 0; k < 3; ++k) v.lo[k] = P->root[k];
     v.W = P->root[3];
     v.level = bx.level; v.parent = bx.parent; v.child_begin = bx.child_begin;
@@ -687,7 +691,7 @@ int build_plan(fmm_plan_s *P, const double *xyz)
     v.perm = P->perm; v.xs = xs; v.ys = ys; v.zs = zs;
     v.U_off = P->off[0]; v.V_off = P->off[1]; v.W_off = P->off[2]; v.X_off = P->off[3];
     v.U_src = P->src[0]; v.W_src = P->src[2]; v.X_src = P->src[3]; v.wsrc = P->wsrc;
-    v.m2l_tgt = slots; v.vslot = vslot; v.leaves = leaves; v.xtgt = xtgt;
+    v.m2l_tgt = slots; v.vslot = vslot; v.leaves = leaves; v.xtgt = xtgt; v.wtgt = wtgt;
     v.lvl_nonleaf = nonleaf; v.lvl_nonleaf_off = lnl_off; v.tab = P->tab; v.rot = P->rot;
     // row `nb` of the folded multipoles is the all-zero operand of absent M2L
     // sources; it is never written by an evaluation
@@ -1102,13 +1106,10 @@ int run_pipeline(fmm_plan_s *const *P, int count, const PlanView *V, int fld, hi
     // downward pass; plans without W lists skip it
     {
         T2.begin(11);
-        for (auto &r : runs) {
-            int w = 0;
-            for (int i = r.first; i < r.second; ++i) w += P[i]->nlist[2] > 0;
-            if (w)
-                launch_m2p(P[r.first]->p, fld, V + r.first,
-                           sub(r.first, r.second, [](const fmm_plan_s *p) { return p->nlist[2] > 0 ? p->nleaves : 0; }), F->side);
-        }
+        for (auto &r : runs) // (by the plan, not the launch: a batch's sums are those of its plans alone)
+            for (int one = 0; one < 2; ++one)
+                launch_m2p(P[r.first]->p, fld, one, V + r.first, sub(r.first, r.second, [one](const fmm_plan_s *p) {
+                    return (p->nwtgt >= kM2POneWave) == one ? p->nwtgt : 0; }), F->side);
         T2.end();
     }
     HIPCHK(hipEventRecord(F->ev_join, F->side));
@@ -1177,7 +1178,7 @@ int run_soft(fmm_plan_s *P, int fld, hipStream_t s)
         T2.end();
         if (part == 1 && P->nlist[2] > 0) { // M2P adds into the near-field sums
             T2.begin(11);
-            launch_soft_m2p(P->p, fld, V, P->nleaves, P->side);
+            launch_soft_m2p(P->p, fld, V, P->nwtgt, P->side);
             T2.end();
         }
         HIPCHK(hipEventRecord(P->ev_join, P->side));

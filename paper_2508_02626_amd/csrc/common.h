@@ -364,7 +364,7 @@ struct PlanView {
     int precision;          // FMM_FP64 / FMM_MIXED
     int mixed_m2l;          // FP32 MFMA M2L
     int depth, D;
-    int32_t n, nboxes, nleaves, nxtgt, nslots;
+    int32_t n, nboxes, nleaves, nxtgt, nwtgt, nslots;
     double lo[3], W;
     const int32_t *level, *parent, *child_begin, *nchild, *first, *count;
     const uint64_t *morton;
@@ -377,6 +377,7 @@ struct PlanView {
     const int32_t *vslot;               // [boxes][189] M2L source per offset slot, or -1
     const int32_t *leaves;              // leaf boxes
     const int32_t *xtgt;                // boxes with a non-empty X list
+    const int32_t *wtgt;                // leaves with a non-empty W list
     const int32_t *lvl_nonleaf;         // non-leaf boxes grouped by level
     const int32_t *lvl_nonleaf_off;     // [depth+2] ranges into lvl_nonleaf
     const OrderTables *tab;             // device copy of the order tables

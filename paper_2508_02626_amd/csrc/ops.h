@@ -45,7 +45,9 @@ void launch_unfold(int p, const PlanView *V, const Bases &B, int leaves_only, hi
 void launch_p2l(int p, const PlanView *V, const Bases &B, hipStream_t s);  // 1 X target/block
 void launch_p2l_transform(const PlanView *V, const Bases &B, hipStream_t s); // 16 X targets x 16 rows/block
 void launch_far(int p, int fld, const PlanView *V, const Bases &B, hipStream_t s);  // 2 leaves/block (L2P + output)
-void launch_m2p(int p, int fld, const PlanView *V, const Bases &B, hipStream_t s);  // 1 leaf/block (W lists)
+// 1 leaf with a W list/block, of four wavefronts or (one) of one
+constexpr int kM2POneWave = 8192; // such leaves of a plan from which it is one
+void launch_m2p(int p, int fld, int one, const PlanView *V, const Bases &B, hipStream_t s);
 // P2P runs in two parts (leaves [0, split) and [split, nleaves)), each
 // overlapping a latency-bound phase of the far field
 __host__ __device__ inline int p2p_split(int nleaves) { return (int)((int64_t)nleaves * 5 / 8) & ~3; }

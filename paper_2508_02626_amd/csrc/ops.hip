@@ -730,12 +730,17 @@ __global__ __launch_bounds__(64) void k_far(const PlanView *V, Bases B)
 // leaf's W list, added to the near-field sums.  It needs only multipoles and
 // the near field, so it runs after the second P2P part on the side stream,
 // next to the downward pass.
-// One block per leaf, whose wavefronts share the W list: leaves with a W list are
-// few (8 to 40% of an adaptive tree's) and their lists long (24 boxes at the median,
-// over 100 at the end), so that one wavefront per leaf left the chip idle behind
-// the longest.  Eight wavefronts are better still where there are few such leaves
-// (40 us against 53 at 17,389 Plummer points) but cost occupancy where there are
-// many (414 us against 340 at 250,000).
+// One block per leaf with a W list (8 to 40% of an adaptive tree's), whose
+// wavefronts share the list: the lists are long (24 boxes at the median, over 100
+// at the end), so that with one wavefront each a launch of few leaves left the chip
+// idle behind the longest.  Eight wavefronts are better still where there are few such
+// leaves (40 us against 53 at 17,389 Plummer points) but cost occupancy where there
+// are many (414 us against 340 at 250,000); from kM2POneWave leaves of a plan on one
+// each is enough, and short lists would leave three of four idle.  Four | one, with the field:
+// 531 leaves (20,000 Plummer points, 64 a leaf, p = 8) 47 | 140 us; 2,887 (300,000,
+// 64, p = 8) 0.17 | 0.28 ms; 9,079 (300,000 uniform, 16, p = 5) 139 | 50 us; 9,926
+// (300,000 Plummer, 16, p = 8) 0.26 | 0.26 ms; 16,102 (4e6, 64, p = 14) 3.0 | 3.2 ms, the
+// step 36.7 | 36.3; 142,190 (300,000 uniform, 2, p = 1) 0.97 | 0.33 ms.
 // A pass takes up to 64 targets; one of at most 32 or 16 targets splits the
 // wavefront into 2 or 4 groups of lanes, each evaluating another box for the same
 // targets.  The sums of groups and wavefronts are added at the end in their order.
@@ -743,26 +748,23 @@ __global__ __launch_bounds__(64) void k_far(const PlanView *V, Bases B)
 // gradient) at about half its rate, the rest the serial chains of the Horner scheme
 // on two or three wavefronts per SIMD.  Two targets per lane (half the LDS reads)
 // or more wavefronts with the rows evaluated in order did not make it faster.
-// One wavefront per leaf -> this: 17,389 Plummer points, p = 8, 165 -> 53 us;
-// 250,000, p = 12, 606 -> 340 us; 4e6, p = 14, 3.07 -> 2.88 ms; 1e6 Gaussian points,
-// p = 10, potentials alone, leaves of up to 128, 809 -> 420 us.
-constexpr int kM2PWaves = 4;
+// A wavefront per leaf and box after box -> this: 17,389 Plummer points, p = 8, 165 ->
+// 52 us; 250,000, p = 12, 635 -> 372 us; 4e6, p = 14, 3.35 -> 3.2 ms; 1e6 Gaussian points,
+// p = 10, potentials alone, leaves of up to 128, 1098 -> 540 us (beside the L2L).
 template <int P> constexpr int kM2PGroups = ncoef(P) <= 288 ? 4 : 2; // (LDS and registers of the boxes)
-template <int P, bool FLD>
-__global__ __launch_bounds__(64 * kM2PWaves) __attribute__((amdgpu_waves_per_eu(P < 12 ? 3 : 2, 8))) void k_m2p(
-    const PlanView *V, Bases B, int block0)
+template <int P, bool FLD, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(P < 12 ? 3 : 2, 8))) void k_m2p(
+    const PlanView *V, Bases B)
 {
-    constexpr int NC = ncoef(P), GM = kM2PGroups<P>, R = (NC + 63) / 64, NW = kM2PWaves;
+    constexpr int NC = ncoef(P), GM = kM2PGroups<P>, R = (NC + 63) / 64;
     constexpr int LDC = (NC + 1) / 2 * 2;
     __shared__ double cm[NW][GM][LDC]; // the boxes' coefficients
     __shared__ double4 sGeo[64];       // centre and width of the W boxes
-    __shared__ double4 sSum[NW - 1][64];
-    const int block = block0 + (int)blockIdx.x;
-    int k = find_plan(B, block);
+    __shared__ double4 sSum[NW > 1 ? NW - 1 : 1][64];
+    int k = find_plan(B, blockIdx.x);
     const PlanView &v = V[k];
-    const int box = v.leaves[block - B.b[k]];
+    const int box = v.wtgt[blockIdx.x - B.b[k]];
     const int64_t w0 = v.W_off[box], w1 = v.W_off[box + 1];
-    if (w0 == w1) return;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const OrderTables &t = *v.tab;
     double cen[3], h;
@@ -1144,7 +1146,8 @@ template <typename T> __global__ void k_zero(T *p, int64_t n)
     case 14: KERNEL<14> __VA_ARGS__; break; case 15: KERNEL<15> __VA_ARGS__; break;  \
     default: KERNEL<16> __VA_ARGS__; break;                                            \
     }
-#define DISPATCH_PF(p, KERNEL, F, ...)                                                            \
+#define TARGS(...) __VA_ARGS__
+#define DISPATCH_PF(p, KERNEL, F, ...) /* F: the template arguments after the order */            \
     switch (p) {                                                                                  \
     case 0: KERNEL<0, F> __VA_ARGS__; break;  case 1: KERNEL<1, F> __VA_ARGS__; break;            \
     case 2: KERNEL<2, F> __VA_ARGS__; break;  case 3: KERNEL<3, F> __VA_ARGS__; break;            \
@@ -1212,15 +1215,15 @@ void launch_p2l_transform(const PlanView *V, const Bases &B, hipStream_t s)
 {
     if (nblk(B)) k_p2l_transform<<<nblk(B), 64, 0, s>>>(V, B);
 }
-void launch_m2p(int p, int fld, const PlanView *V, const Bases &B, hipStream_t s)
+void launch_m2p(int p, int fld, int one, const PlanView *V, const Bases &B, hipStream_t s)
 {
-    // a launch holds fewer than 2^32 threads: at four wavefronts a leaf, larger
-    // plans and batches take several
-    constexpr unsigned kMost = 0xffffffffu / (64 * kM2PWaves);
-    for (unsigned b0 = 0; b0 < nblk(B); b0 += kMost) {
-        const unsigned n = nblk(B) - b0 < kMost ? nblk(B) - b0 : kMost;
-        if (fld) DISPATCH_PF(p, k_m2p, true, <<<n, 64 * kM2PWaves, 0, s>>>(V, B, (int)b0))
-        else DISPATCH_PF(p, k_m2p, false, <<<n, 64 * kM2PWaves, 0, s>>>(V, B, (int)b0))
+    if (!nblk(B)) return;
+    if (one) {
+        if (fld) DISPATCH_PF(p, k_m2p, TARGS(true, 1), <<<nblk(B), 64, 0, s>>>(V, B))
+        else DISPATCH_PF(p, k_m2p, TARGS(false, 1), <<<nblk(B), 64, 0, s>>>(V, B))
+    } else {
+        if (fld) DISPATCH_PF(p, k_m2p, TARGS(true, 4), <<<nblk(B), 256, 0, s>>>(V, B))
+        else DISPATCH_PF(p, k_m2p, TARGS(false, 4), <<<nblk(B), 256, 0, s>>>(V, B))
     }
 }
 void launch_far(int p, int fld, const PlanView *V, const Bases &B, hipStream_t s)

@@ -26,5 +26,5 @@ constexpr int kSoftSymOrder = 4, kSoftSymMaxOrder = 8;
 int soft_sym_ld(int p);
 void launch_m2l_soft(int p, const PlanView *V, const SoftGrid &G, double *Ms, int nboxes, hipStream_t s);
 void launch_soft_p2l(int p, const PlanView *V, int nxtgt, hipStream_t s);   // 1 X target/block
-void launch_soft_m2p(int p, int fld, const PlanView *V, int nleaves, hipStream_t s); // 1 leaf/block (W lists)
+void launch_soft_m2p(int p, int fld, const PlanView *V, int nwtgt, hipStream_t s); // 1 leaf with a W list/block
 } // namespace fmm

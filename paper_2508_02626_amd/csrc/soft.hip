@@ -1061,9 +1061,8 @@ __global__ __launch_bounds__(64) void k_soft_m2p(const PlanView *V)
     constexpr int NC = ncoef(P), RC = (NC + 63) / 64;
     __shared__ double cm[2][NC];
     const PlanView &v = V[0];
-    const int box = v.leaves[blockIdx.x], lane = threadIdx.x;
+    const int box = v.wtgt[blockIdx.x], lane = threadIdx.x;
     const int64_t w0 = v.W_off[box], w1 = v.W_off[box + 1];
-    if (w0 == w1) return;
     const int f = v.first[box], cnt = v.count[box];
     for (int s0 = 0; s0 < cnt; s0 += 64) {
         const bool act = s0 + lane < cnt;
@@ -1170,12 +1169,12 @@ void launch_soft_p2l(int p, const PlanView *V, int nxtgt, hipStream_t s)
 #undef T_
 }
 
-void launch_soft_m2p(int p, int fld, const PlanView *V, int nleaves, hipStream_t s)
+void launch_soft_m2p(int p, int fld, const PlanView *V, int nwtgt, hipStream_t s)
 {
-    if (nleaves <= 0) return;
+    if (nwtgt <= 0) return;
 #define T_(PP)                                              \
-    if (fld) k_soft_m2p<PP, true><<<nleaves, 64, 0, s>>>(V); \
-    else k_soft_m2p<PP, false><<<nleaves, 64, 0, s>>>(V)
+    if (fld) k_soft_m2p<PP, true><<<nwtgt, 64, 0, s>>>(V); \
+    else k_soft_m2p<PP, false><<<nwtgt, 64, 0, s>>>(V)
     SOFT_SWITCH(p, T_)
 #undef T_
 }

@@ -6,7 +6,7 @@ namespace fmm {
 size_t scan_scratch_bytes(int64_t n);
 // out[0..n]: exclusive prefix sums of in[0..n), out[n] = total
 void scan_exclusive(const int64_t *in, int64_t *out, int64_t n, int64_t *scratch, hipStream_t s);
-constexpr int kMaxScanBatch = 8;
+constexpr int kMaxScanBatch = 9;
 size_t scan_multi_scratch_bytes(int64_t n, int count);
 // count (<= kMaxScanBatch) scans of length n in one set of launches
 void scan_exclusive_multi(const int64_t *const *in, int64_t *const *out, int count, int64_t n,

@@ -46,10 +46,11 @@ void uwlist(const TreeArgs &a, const int32_t *coll, int which, int64_t *ucnt, co
             int32_t *usrc, int64_t *wcnt, const int64_t *woff, int32_t *wsrc, int64_t *xcnt, hipStream_t s);
 void w_pairs(const int64_t *woff, const int32_t *wsrc, int nboxes, uint64_t *key, int32_t *val, int32_t *used,
              hipStream_t s);
-void flags(const BoxArrays &bx, int nboxes, const int64_t *xcnt, const int64_t *vcnt, int64_t *fleaf,
-           int64_t *fnon, int64_t *fx, int64_t *fv, hipStream_t s);
-// four lists of flagged boxes
-void compact4(const int64_t *const *flag, const int64_t *const *pos, int nboxes, int32_t *const *out, hipStream_t s);
+// work lists: leaves, non-leaves, boxes with an X, a V, a W list
+constexpr int kWorkLists = 5;
+void flags(const BoxArrays &bx, int nboxes, const int64_t *xcnt, const int64_t *vcnt, const int64_t *wcnt,
+           int64_t *const *flag, hipStream_t s);
+void compact(const int64_t *const *flag, const int64_t *const *pos, int nboxes, int32_t *const *out, hipStream_t s);
 void fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s);
 constexpr int kOctOffsetInts = 512; // ints of m2l_tiles' octoff scratch
 // by_level: no tile holds targets of two levels

@@ -803,29 +803,34 @@ void w_pairs(const int64_t *woff, const int32_t *wsrc, int nboxes, uint64_t *key
 
 // ---------------- work lists ----------------
 // Work-list membership of every box: leaves, non-leaves, boxes with an X
-// list, boxes with a V list; compaction via exclusive scans of the flags.
+// list, with a V list, with a W list; compaction via exclusive scans of the flags.
+struct WorkFlags {
+    int64_t *f[kWorkLists];
+};
 __global__ __launch_bounds__(256) void k_flags(const BoxArrays bx, int nboxes, const int64_t *xcnt,
-                                               const int64_t *vcnt, int64_t *fleaf, int64_t *fnon,
-                                               int64_t *fx, int64_t *fv)
+                                               const int64_t *vcnt, const int64_t *wcnt, WorkFlags o)
 {
     int b = blockIdx.x * 256 + threadIdx.x;
     if (b >= nboxes) return;
     const bool leaf = bx.nchild[b] == 0;
-    fleaf[b] = leaf;
-    fnon[b] = !leaf;
-    fx[b] = xcnt[b] > 0;
-    fv[b] = vcnt[b] > 0;
+    o.f[0][b] = leaf;
+    o.f[1][b] = !leaf;
+    o.f[2][b] = xcnt[b] > 0;
+    o.f[3][b] = vcnt[b] > 0;
+    o.f[4][b] = wcnt[b] > 0;
 }
 
-void flags(const BoxArrays &bx, int nboxes, const int64_t *xcnt, const int64_t *vcnt, int64_t *fleaf,
-           int64_t *fnon, int64_t *fx, int64_t *fv, hipStream_t s)
+void flags(const BoxArrays &bx, int nboxes, const int64_t *xcnt, const int64_t *vcnt, const int64_t *wcnt,
+           int64_t *const *flag, hipStream_t s)
 {
-    k_flags<<<ceil_div(nboxes, 256), 256, 0, s>>>(bx, nboxes, xcnt, vcnt, fleaf, fnon, fx, fv);
+    WorkFlags o;
+    for (int w = 0; w < kWorkLists; ++w) o.f[w] = flag[w];
+    k_flags<<<ceil_div(nboxes, 256), 256, 0, s>>>(bx, nboxes, xcnt, vcnt, wcnt, o);
 }
 
 struct CompactBatch {
-    const int64_t *flag[4], *pos[4];
-    int32_t *out[4];
+    const int64_t *flag[kWorkLists], *pos[kWorkLists];
+    int32_t *out[kWorkLists];
 };
 __global__ __launch_bounds__(256) void k_compact(CompactBatch c, int nboxes)
 {
@@ -835,11 +840,11 @@ __global__ __launch_bounds__(256) void k_compact(CompactBatch c, int nboxes)
     if (c.flag[w][b]) c.out[w][c.pos[w][b]] = b;
 }
 
-void compact4(const int64_t *const *flag, const int64_t *const *pos, int nboxes, int32_t *const *out, hipStream_t s)
+void compact(const int64_t *const *flag, const int64_t *const *pos, int nboxes, int32_t *const *out, hipStream_t s)
 {
     CompactBatch c{};
-    for (int w = 0; w < 4; ++w) { c.flag[w] = flag[w]; c.pos[w] = pos[w]; c.out[w] = out[w]; }
-    k_compact<<<dim3(ceil_div(nboxes, 256), 4), 256, 0, s>>>(c, nboxes);
+    for (int w = 0; w < kWorkLists; ++w) { c.flag[w] = flag[w]; c.pos[w] = pos[w]; c.out[w] = out[w]; }
+    k_compact<<<dim3(ceil_div(nboxes, 256), kWorkLists), 256, 0, s>>>(c, nboxes);
 }
 
 __global__ void k_fill_i32(int32_t *p, int64_t n, int32_t v)
