@@ -55,14 +55,14 @@ TARGET_SIGMA = 1e-7
 # HBM bytes per launch of the dominant M2L kernel, from rocprofv3 FETCH_SIZE
 # and WRITE_SIZE scaled by a plain-copy calibration (read x2.0, write x1.0;
 # profiles/).  Each figure is valid only for the kernel sources it was
-# measured on (kernel, shared header, tile order): a different fingerprint
+# measured on (kernel, shared headers, tile order): a different fingerprint
 # reports null.
 M2L_TRAFFIC = {
-    "uniform1m": {"fingerprint": "3c89b53399f58b31", "bytes": (1296.29 + 153.34) * 1e6},
-    "plummer4m_p14": {"fingerprint": "3c89b53399f58b31", "bytes": (33599.88 + 998.38) * 1e6},
+    "uniform1m": {"fingerprint": "7d7f921c4806666d", "bytes": (1293.59 + 153.31) * 1e6},
+    "plummer4m_p14": {"fingerprint": "7d7f921c4806666d", "bytes": (33929.08 + 1127.08) * 1e6},
 }
 M2L_SOURCES = ("paper_2508_02626_amd/csrc/m2l.hip", "paper_2508_02626_amd/csrc/common.h",
-               "paper_2508_02626_amd/csrc/m2l_tiles.hip")
+               "paper_2508_02626_amd/csrc/sym_engine.h", "paper_2508_02626_amd/csrc/m2l_tiles.hip")
 
 
 def m2l_fingerprint():
